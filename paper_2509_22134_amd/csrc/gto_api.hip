@@ -318,7 +318,7 @@ constexpr int kFusedMaxK = 16;
 
 struct FusedPlan {
   int64_t M;
-  int n_tiles, groups, patch_rows, patch_cols, n_slots;
+  int n_tiles, groups, patch_rows, patch_cols;
   size_t off_s, off_m, off_c, off_v, off_i, bytes;
 };
 
@@ -331,19 +331,18 @@ int check_fused(const gto_config *c, const void *hidden, int hidden_dim, const v
   return GTO_OK;
 }
 
-// Launch geometry of the row pass (see the work distribution in gto_fused.hip): `groups` groups of
-// patch_rows x patch_cols workgroups, each row with groups * patch_cols partial results.  By default 8 groups
-// of 8 x 4: one group per XCD, one workgroup per compute unit (8 x 4 and 4 x 8 take the same time; 8 x 4 streams
-// the head half as often, fetches a quarter less from the fabric and leaves half as many partial results).
+// Launch geometry of the row pass (see the work distribution in gto_fused.hip): `groups` groups of 32 workgroups.
+// By default 8 groups, one per XCD and one workgroup per compute unit, with a patch shape that follows the row
+// count (8 x 4 for many rows: it takes the same time as 4 x 8, streams the head half as often, fetches a quarter
+// less from the fabric and leaves half as many partial results).
 FusedPlan fused_plan(const gto_config *c, int64_t M, int ktop) {
   FusedPlan p{};
   p.M = M;
   p.n_tiles = (c->V + 255) / 256;
   p.groups = c->fused_groups > 0 ? c->fused_groups : 8;
-  p.patch_rows = c->fused_layout == 0 ? 8 : 4;
-  p.patch_cols = c->fused_layout == 0 ? 4 : 8;
-  p.n_slots = p.groups * p.patch_cols;
-  const size_t rows = (size_t)M * p.n_slots;
+  p.patch_rows = c->fused_layout == 0 ? 0 : 4;
+  p.patch_cols = c->fused_layout == 0 ? 0 : 8;
+  const size_t rows = (size_t)gto::fused_partials(M, p.groups, p.patch_rows, p.patch_cols);
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   p.off_s = 0;
   p.off_m = up(p.off_s + rows * sizeof(double));
@@ -797,13 +796,15 @@ int gto_ppo_surrogate_bwd_fused(const gto_config *cfg, const gto_tree *tree_cur,
 // count, the two bf16 planes [R d, V], the split partials [splits, R d, hidden]
 struct DhWs {
   int n_splits, slabs_per_split, m_blocks, h_blocks;
+  int64_t pitch;
   size_t off_list_p, off_list_slot, off_count, off_s, off_hi, off_lo, off_partial, bytes;
 };
 DhWs dh_ws(const gto_config *c, int hidden_dim) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   DhWs L{};
   const size_t rd = (size_t)c->R * c->d;
-  const int slabs = 2 * (c->V / 32);
+  L.pitch = ((int64_t)c->V + 63) & ~(int64_t)63;
+  const int slabs = (int)(2 * (L.pitch / 64));
   const int want = 8;                               // splits of the contraction, so that few rows still fill the chip
   L.slabs_per_split = (slabs + want - 1) / want;
   L.n_splits = (slabs + L.slabs_per_split - 1) / L.slabs_per_split;
@@ -813,9 +814,10 @@ DhWs dh_ws(const gto_config *c, int hidden_dim) {
   L.off_list_p = off; off += up(rd * sizeof(int32_t));
   L.off_list_slot = off; off += up(rd * sizeof(int32_t));
   L.off_count = off; off += 256;
-  L.off_s = off; off += up(rd * 64 * sizeof(double));     // at most 64 partial results per row
-  L.off_hi = off; off += up(rd * (size_t)c->V * sizeof(uint16_t));
-  L.off_lo = off; off += up(rd * (size_t)c->V * sizeof(uint16_t));
+  const FusedPlan p = fused_plan(c, (int64_t)rd, 1);
+  L.off_s = off; off += p.off_m;                         // the plane pass's partial sums
+  L.off_hi = off; off += up(rd * (size_t)L.pitch * sizeof(uint16_t));
+  L.off_lo = off; off += up(rd * (size_t)L.pitch * sizeof(uint16_t));
   L.off_partial = off; off += up((size_t)L.n_splits * rd * hidden_dim * sizeof(float));
   L.bytes = off;
   return L;
@@ -869,14 +871,14 @@ int gto_ppo_surrogate_bwd_fused_dh(const gto_config *cfg, const gto_tree *tree_c
     a.d = cfg->d; a.kslots = cfg->k; a.ktop = 1; a.M = rd; a.m_dev = count; a.row_list = list_slot; a.out_by_list = 1;
     set_geometry(a, p);
     a.list_p = list_p; a.coef = fwd->coef; a.lse_by_slot = draft_stats_cur->row_lse; a.g = cfg->g;
-    a.plane_hi = hi; a.plane_lo = lo; a.sel_tok = tree_cur->sel_tok; a.path_node = path_cur->path_node;
+    a.plane_hi = hi; a.plane_lo = lo; a.plane_pitch = L.pitch; a.sel_tok = tree_cur->sel_tok; a.path_node = path_cur->path_node;
     a.part_s = reinterpret_cast<double *>(base + L.off_s);
     ProfScope ps("fused_rows_bwd_planes", st);
     gto::launch_fused_rows(a, st);
   }
   {
     gto::FusedDhArgs a{};
-    a.plane_hi = hi; a.plane_lo = lo; a.w_hv = w_draft_hv; a.w_vh = w_draft_vh;
+    a.plane_hi = hi; a.plane_lo = lo; a.plane_pitch = L.pitch; a.w_hv = w_draft_hv; a.w_vh = w_draft_vh;
     a.hidden_dim = hidden_dim; a.V = cfg->V; a.d = cfg->d; a.g = cfg->g; a.M = rd; a.m_dev = count;
     a.m_blocks = L.m_blocks; a.h_blocks = L.h_blocks; a.n_splits = L.n_splits; a.slabs_per_split = L.slabs_per_split;
     a.partial = reinterpret_cast<float *>(base + L.off_partial);

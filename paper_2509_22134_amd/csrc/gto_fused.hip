@@ -2,48 +2,42 @@
 // reduced to the row statistics (max, log-sum-exp, exact top-k) in the epilogue, so the logits
 // never reach HBM.
 //
-//  k_fused_rows  : 256 x 256 output tile per workgroup iteration (4 waves, each 128 x 128 as 4 x 4
-//                  MFMA 32x32x16 bf16 tiles, fp32 accumulators).  K slabs of 32 go from global
-//                  memory straight into a ring of four LDS stages (no register staging), three
-//                  slabs in flight while one is multiplied.  The launch is persistent (one
-//                  workgroup per compute unit); a workgroup keeps its 256 rows while it moves
-//                  along a patch row of the tile grid.  After each tile the accumulators are staged
-//                  through LDS column-major; in the statistics passes thread t owns row t and folds
-//                  its 256 new logits into its running (max, sum, top-k list) in registers; in the
-//                  writing passes (gradient rows, bf16 planes, stored logits) the eight lanes of a
-//                  row write contiguous bytes.
+//  k_fused_rows  : 256 x 256 output tile per workgroup iteration: 8 waves, two per SIMD, each 128 x 64
+//                  as 8 x 4 MFMA 16x16x32 bf16 tiles with fp32 accumulators.  K slabs of 64 go from
+//                  global memory straight into one of two LDS stages; the two waves of a SIMD take turns
+//                  between the matrix cores and everything else (see the main loop).  The launch is
+//                  persistent (one workgroup per compute unit); a workgroup keeps its 256 rows while it
+//                  moves along a patch row of the tile grid.  After each tile the accumulators are staged
+//                  through LDS column-major; in the statistics passes threads t and t + 256 own row t
+//                  (half of the columns each) and fold the new logits into a running (max, sum, top-k
+//                  list) in registers; in the writing passes (gradient rows, bf16 planes, stored logits)
+//                  the eight lanes of a row write contiguous bytes.
 //  k_fused_merge : combines the partial results of a row (one per group and column phase) into the
 //                  final statistics.
 //  k_gather_dot  : single logits (hidden row . W row) for the few (row, token) pairs the reward
 //                  and the surrogate need.
+#include <algorithm>
+
 #include "gto_device.h"
 #include "gto_kernels.h"
 
 namespace gto {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int FBM = 256, FBN = 256;
-constexpr int FBK = 32;                            // k extent of one LDS stage
+constexpr int FTHREADS = 512;                      // 8 waves: two groups of four, one wave of each group per SIMD
+constexpr int FBK = 64;                            // k extent of one LDS stage (a whole 128-byte line per row)
 constexpr int FROWB = FBK * 2;                     // bytes per staged row (bf16)
-constexpr int FSTAGE_B = (FBM + FBN) * FROWB;      // bytes per stage: 256 hidden rows, then 256 W rows
-constexpr int FNST = 4;                            // LDS stages: one being multiplied, FNST-1 landing (3 and 5 measured slower)
+constexpr int FOP_B = FBM * FROWB;                 // bytes of one operand in a stage
+constexpr int FSTAGE_B = 2 * FOP_B;                // 256 hidden rows, then 256 W rows
 constexpr int FKT = 16;                            // capacity of the per-thread top list
 constexpr int FSTG_CM = FBM + 4;                   // staging column stride (floats), column-major staging
-constexpr size_t kFusedLdsBytes = (size_t)FNST * FSTAGE_B;
+constexpr size_t kFusedLdsBytes = (size_t)2 * FSTAGE_B;
+static_assert(FBM == FBN, "the two operands share one stage layout");
 static_assert(kFusedLdsBytes >= (size_t)64 * FSTG_CM * sizeof(float), "staging area must fit");
 static_assert(63 * FSTG_CM * sizeof(float) < 65536, "a row's 64 staged columns are reached with immediate offsets");
-static_assert(FNST == 4, "the wait counts and the issue order of the main loop are written for this ring");
-
-// wait until at most n of this wave's vector memory operations are outstanding (n known at compile time)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N == 0 || N == 8 || N == 16, "counts used by the slab ring");
-  if (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  if (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-}
+static_assert(kFusedLdsBytes >= (size_t)FBM * (sizeof(double) + 8 + FKT * 8), "a flush hands 256 row states over");
 
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave lands at lds_addr + 16 l
 // (lds_addr is wave-uniform; the compiler moves it into M0); counted by vmcnt.
@@ -86,123 +80,173 @@ __device__ __forceinline__ void list_insert(float (&v)[KT], int (&id)[KT], float
   }
 }
 
-// ---- the GEMM main loop: acc += A . B^T over kt_count k slabs of 32, for the 256 x 256 tile of the
-// workgroup; wave (wm, wn) owns the 128 x 128 quadrant as 4 x 4 MFMA 32x32x16 tiles.
+// ---- the GEMM main loop: acc += A . B^T over n_slabs k slabs of 64, for the 256 x 256 tile of the workgroup.
+// Wave (wm, wn) = (wave / 4, wave % 4) owns rows 128 wm .. + 127 and 64 columns as 8 x 4 MFMA 16x16x32 tiles; its
+// tile (i, j) holds rows 128 wm + 16 i and columns 64 j + 16 wn (the callers lay the column operand out so): the
+// j-th column tiles of the four column waves are 64 consecutive columns, what one epilogue phase takes.
 //
-// K slab s lands in ring stage s % 4 (global memory -> LDS directly); every wave issues 4 loads per
-// operand and slab (load j = the 16-row group 64 wave + 16 j).  The matrix pipe is the unit to keep busy
-// and this wave is the only one on its SIMD, so the instruction stream is laid out by hand: every MFMA is
-// followed by at most one memory instruction (pinned by scheduling barriers), which issues while the
-// MFMA executes.  One slab:
-//   first half  (k units 0, 1): after MFMA 0..7 the fragment reads of the second half (the four W
-//               fragments first: its first MFMA row needs them all); then the wait until slab s+1 has
-//               landed, and the barrier
-//   second half (k units 2, 3): after MFMA 0..7 the first-half fragments of slab s+1; after MFMA 8..15
-//               the loads of slab s+3 (hidden states, then W): a slab is requested two and a half slabs
-//               (about 5000 clocks) before its first use, which is what a miss in the L2 needs here
-struct SlabRing {
-  unsigned wbase;              // LDS byte address of this wave's 4 KB landing area inside stage 0
-  const unsigned char *ldsb;   // the ring
-  int fa_base, fb_base;        // this lane's fragment byte offsets inside a stage (k units 0 / 1)
+// What bounds it: the matrix pipe, as long as nothing else stands in its way.  One wave per SIMD that issues
+// fragment reads and loads between its MFMAs stalls the pipe whenever one of those instructions is held up
+// (measured: 0.66 busy, 110 ms for 58 368 x 8192 x 128 256).  So two waves share a SIMD and take turns: the waves of group 0 (wm = 0) and of group 1
+// are half a phase apart, and between two barriers one group issues 16 MFMAs (256 matrix-pipe cycles) while the
+// other reads fragments and requests loads for its next 16.  A slab is four such phases, one per quadrant of the
+// wave's tile, in an order in which each quadrant shares an operand half with the one before:
+//     phase   MFMA quadrant      fragments read before it      load requested before it (slab s + 2)
+//       0     A0 x B0            A0 (8 reads)                  B0
+//       1     A0 x B1            B1 (4)                        A0
+//       2     A1 x B1            A1 (8)                        B1
+//       3     A1 x B0            B0 of slab s + 1 (4)          A1
+// (A0 / A1: the first and second 64 rows of each row half; B0 / B1: the first and second 32 columns of each column
+// wave.)  A quarter of a stage is requested again as soon as both groups have read it, so two stages of 64 KB keep
+// every load in flight for a slab and a half (about 3000 clocks).  Every phase ends its reading part with
+// `vmcnt(12)`: at most the six newest requests (two instructions each) are still out, which is exactly what the
+// next phase does not read; the barrier extends that to the other waves' shares.
+// Measured: 58 368 x 8192 x 128 256 with the statistics epilogue in 89.4 ms (1.37 PFLOP/s; 110.0 ms with one wave
+// per SIMD and 32x32x16 tiles), the writing passes 2.96 ms (3.80), 2.28 ms (2.99).
+struct Slab {
+  unsigned wA, wB;               // LDS byte address of this wave's share of A0 / B0 in stage 0
+  const unsigned char *ldsb;     // the stages
+  int fA, fB;                    // byte offset of this lane's fragments in stage 0, k step 0 (k step 1: offset ^ 64)
 };
 
-// LOAD3: slab s+3 exists and is requested here.  PEND2: slab s+2 exists (its 8 loads are in flight at the
-// wait).  NEXT: slab s+1 exists.
-template <bool LOAD3, bool PEND2, bool NEXT>
-__device__ __forceinline__ void slab_step(f32x16 (&acc)[4][4], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][4],
-                                          const SlabRing &r, const uint16_t *(&ap)[4], const uint16_t *(&bp)[4],
-                                          int stage) {
-  const int s1 = (stage + 1) % FNST, s3 = (stage + 3) % FNST;
-  const unsigned char *sS = r.ldsb + stage * FSTAGE_B;
-  const unsigned char *nS = r.ldsb + s1 * FSTAGE_B;
-#pragma unroll
-  for (int idx = 0; idx < 16; ++idx) {
-    const int i = idx >> 2, j = (i & 1) ? 3 - (idx & 3) : (idx & 3);    // boustrophedon: one operand changes per MFMA
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][i], fb[0][j], acc[i][j], 0, 0, 0);
-    if (idx < 4) {
-      fb[1][idx] = *reinterpret_cast<const bf16x8 *>(sS + (r.fb_base ^ 32) + idx * 32 * FROWB);
-    } else if (idx < 8) {
-      fa[1][idx - 4] = *reinterpret_cast<const bf16x8 *>(sS + (r.fa_base ^ 32) + (idx - 4) * 32 * FROWB);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (NEXT) {
-    // this wave's share of slab s+1 has landed when at most the 8 loads of slab s+2 are still out; the
-    // barrier extends that to the other waves' shares, and tells that every wave is past its reads of
-    // slab s-1, whose stage the loads below overwrite
-    if (PEND2) wait_vmcnt<8>();
-    else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int idx = 0; idx < 16; ++idx) {
-    const int i = idx >> 2, j = (i & 1) ? 3 - (idx & 3) : (idx & 3);
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][i], fb[1][j], acc[i][j], 0, 0, 0);
-    if (NEXT) {
-      if (idx < 4) fb[0][idx] = *reinterpret_cast<const bf16x8 *>(nS + r.fb_base + idx * 32 * FROWB);
-      else if (idx < 8) fa[0][idx - 4] = *reinterpret_cast<const bf16x8 *>(nS + r.fa_base + (idx - 4) * 32 * FROWB);
-    }
-    if (LOAD3) {
-      if (idx >= 8 && idx < 12) {
-        load_to_lds16(r.wbase + s3 * FSTAGE_B + (idx - 8) * 1024, ap[idx - 8]);
-        ap[idx - 8] += FBK;
-      } else if (idx >= 12) {
-        load_to_lds16(r.wbase + s3 * FSTAGE_B + FBM * FROWB + (idx - 12) * 1024, bp[idx - 12]);
-        bp[idx - 12] += FBK;
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
+template <int VM>
+__device__ __forceinline__ void end_of_reads() {
+  // all fragment reads have returned (the other group may request over what they read), loads as counted
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(VM) : "memory");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
 }
 
-// ap[j] / bp[j]: this lane's global address, in slab 0, for load j of the row operand / the column
-// operand: the 16 bytes of row ld_row + 16 j at k unit ld_unit (see the callers); both advance by one slab
-// per load.  Every wave of the workgroup calls this with the same kt_count >= 1; on return all fragment
-// reads of the caller's wave are done and nothing of this call is in flight.
-__device__ __forceinline__ void tile_mainloop(f32x16 (&acc)[4][4], uint16_t *lds, unsigned wbase, int lane, int wm,
-                                              int wn, int kt_count, const uint16_t *(&ap)[4],
-                                              const uint16_t *(&bp)[4]) {
-  SlabRing r;
-  r.wbase = wbase;
+template <int I0, int J0>
+__device__ __forceinline__ void quadrant(f32x4 (&acc)[8][4], const bf16x8 (&fa)[2][4], const bf16x8 (&fb)[2][2]) {
+  __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const int j = (i & 1) ? 1 - jj : jj;        // one operand changes per MFMA
+        acc[I0 + i][J0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[I0 + i][J0 + j], 0, 0, 0);
+      }
+  __builtin_amdgcn_s_setprio(0);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// N 16-row fragment tiles from `off` bytes behind this lane's fragment offset (both k steps)
+template <int N>
+__device__ __forceinline__ void read_frags(bf16x8 (&f)[2][N], const unsigned char *ldsb, int frag, int off) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int t = 0; t < N; ++t)
+      f[h][t] = *reinterpret_cast<const bf16x8 *>(ldsb + (frag ^ (64 * h)) + off + t * 16 * FROWB);
+}
+// this wave's two load instructions of one quarter of a stage; the pointers move on by one slab
+__device__ __forceinline__ void request(unsigned lds_addr, const uint16_t *&p0, const uint16_t *&p1) {
+  load_to_lds16(lds_addr, p0);
+  load_to_lds16(lds_addr + 1024, p1);
+  p0 += FBK;
+  p1 += FBK;
+}
+
+// One slab.  LOAD: slab s + 2 exists and is requested.  NEXT: slab s + 1 exists.  V0..V3: outstanding load
+// instructions allowed at the end of each phase's reads.  x holds B0 on entry; y receives B1, then slab s + 1's B0.
+template <bool LOAD, bool NEXT, int V0, int V1, int V2, int V3>
+__device__ __forceinline__ void slab_step(f32x4 (&acc)[8][4], bf16x8 (&fa)[2][4], bf16x8 (&x)[2][2], bf16x8 (&y)[2][2],
+                                          const Slab &r, const uint16_t *(&ap)[4], const uint16_t *(&bp)[4], int stage) {
+  const int off = stage * FSTAGE_B, nxt = FSTAGE_B - off;
+  read_frags<4>(fa, r.ldsb, r.fA, off);
+  if (LOAD) request(r.wB + off, bp[0], bp[1]);
+  end_of_reads<V0>();
+  quadrant<0, 0>(acc, fa, x);
+  read_frags<2>(y, r.ldsb, r.fB, off + 32 * FROWB);
+  if (LOAD) request(r.wA + off, ap[0], ap[1]);
+  end_of_reads<V1>();
+  quadrant<0, 2>(acc, fa, y);
+  read_frags<4>(fa, r.ldsb, r.fA, off + 64 * FROWB);
+  if (LOAD) request(r.wB + off + 32 * FROWB, bp[2], bp[3]);
+  end_of_reads<V2>();
+  quadrant<4, 2>(acc, fa, y);
+  if (NEXT) read_frags<2>(y, r.ldsb, r.fB, nxt);
+  if (LOAD) request(r.wA + off + 64 * FROWB, ap[2], ap[3]);
+  end_of_reads<V3>();
+  quadrant<4, 0>(acc, fa, x);
+}
+
+// Which rows of the two operands this lane fetches: load i of quarter A0 is tile row a_row(i), of A1 a_row(i) + 64;
+// of B0 staged column b_row(i), of B1 b_row(i) + 32; staged column c is the operand's row b_col(c).  The 16 bytes
+// at k unit k_unit(i) of that row land at unit lane % 8, which spreads the fragment reads (16 rows at one k unit)
+// over all LDS banks.
+struct LaneMap {
+  int wave, lane;
+  __device__ __forceinline__ int a_row(int i) const { return (wave >> 2) * 128 + (wave & 3) * 16 + 8 * i + (lane >> 3); }
+  __device__ __forceinline__ int b_row(int i) const { return (wave >> 1) * 64 + (wave & 1) * 16 + 8 * i + (lane >> 3); }
+  __device__ __forceinline__ int k_unit(int i) const { return (lane & 7) ^ (4 * i + (lane >> 4)); }
+  // staged column 64 wn + 16 j + t <-> operand row 64 j + 16 wn + t
+  __device__ static __forceinline__ int b_col(int c) { return ((c >> 4) & 3) * 64 + (c >> 6) * 16 + (c & 15); }
+};
+
+// ap / bp: this lane's global addresses, in slab 0, of loads A0.0, A0.1, A1.0, A1.1 and B0.0, B0.1, B1.0, B1.1.
+// Every wave of the workgroup calls this with the same n_slabs >= 1; on return all waves' fragment reads are done
+// and nothing of this call is in flight.
+__device__ __forceinline__ void tile_mainloop(f32x4 (&acc)[8][4], uint16_t *lds, int wave, int lane, int n_slabs,
+                                              const uint16_t *(&ap)[4], const uint16_t *(&bp)[4]) {
+  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)lds;
+  const int wm = wave >> 2, wn = wave & 3;
+  Slab r;
+  r.wA = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)(wm * 128 + (wave & 3) * 16) * FROWB);
+  r.wB = __builtin_amdgcn_readfirstlane(lds_base + FOP_B + (unsigned)((wave >> 1) * 64 + (wave & 1) * 16) * FROWB);
+  const int fl = (lane & 15) * FROWB + (((lane >> 4) ^ (lane >> 1)) & 3) * 16 + (lane & 8) * 8;
   r.ldsb = reinterpret_cast<const unsigned char *>(lds);
-  // Fragment byte offsets of this lane inside a stage: row (lane & 31) of each 32-row tile; the
-  // 16-byte unit 2 h + (lane >> 5) of k half h sits at unit ^ ((row / 4) % 4).
-  const int fsw = ((lane >> 5) ^ ((lane >> 2) & 3)) * 16;
-  r.fa_base = (wm * 128 + (lane & 31)) * FROWB + fsw;
-  r.fb_base = (FBM + wn * 128 + (lane & 31)) * FROWB + fsw;
-  __syncthreads();                           // the previous user of the ring (an epilogue's staging area) is done
-  // prologue: slabs 0, 1 and 2
+  r.fA = wm * 128 * FROWB + fl;
+  r.fB = FOP_B + wn * 64 * FROWB + fl;
+  __syncthreads();                           // the previous user of the stages (an epilogue's staging area) is done
 #pragma unroll
-  for (int s_ = 0; s_ < 3; ++s_)
-    if (s_ < kt_count) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { load_to_lds16(wbase + s_ * FSTAGE_B + j * 1024, ap[j]); ap[j] += FBK; }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { load_to_lds16(wbase + s_ * FSTAGE_B + FBM * FROWB + j * 1024, bp[j]); bp[j] += FBK; }
+  for (int s_ = 0; s_ < 2; ++s_)
+    if (s_ < n_slabs) {
+      request(r.wB + s_ * FSTAGE_B, bp[0], bp[1]);
+      request(r.wA + s_ * FSTAGE_B, ap[0], ap[1]);
+      request(r.wB + s_ * FSTAGE_B + 32 * FROWB, bp[2], bp[3]);
+      request(r.wA + s_ * FSTAGE_B + 64 * FROWB, ap[2], ap[3]);
     }
-  // slab 0 landed; the later ones stay in flight
-  if (kt_count > 2) wait_vmcnt<16>();
-  else if (kt_count > 1) wait_vmcnt<8>();
-  else wait_vmcnt<0>();
-  __syncthreads();
-  bf16x8 fa[2][4], fb[2][4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    fa[0][t] = *reinterpret_cast<const bf16x8 *>(r.ldsb + r.fa_base + t * 32 * FROWB);
-    fb[0][t] = *reinterpret_cast<const bf16x8 *>(r.ldsb + r.fb_base + t * 32 * FROWB);
+  bf16x8 fa[2][4], x[2][2], y[2][2];
+  if (n_slabs > 1) end_of_reads<12>();       // B0 and A0 of slab 0 have landed
+  else end_of_reads<4>();
+  read_frags<2>(x, r.ldsb, r.fB, 0);
+  if (wm) __builtin_amdgcn_s_barrier();      // group 1 runs half a phase behind group 0
+  int s = 0;
+  for (; s + 3 < n_slabs; s += 2) {          // whole pairs of slabs whose second successors exist
+    slab_step<true, true, 12, 12, 12, 12>(acc, fa, x, y, r, ap, bp, 0);
+    slab_step<true, true, 12, 12, 12, 12>(acc, fa, y, x, r, ap, bp, 1);
   }
-  // slabs whose third successor exists request it; the last three request nothing
-  int kt = 0;
-  for (; kt + 3 < kt_count; ++kt) slab_step<true, true, true>(acc, fa, fb, r, ap, bp, kt & 3);
-  if (kt + 2 < kt_count) { slab_step<false, true, true>(acc, fa, fb, r, ap, bp, kt & 3); ++kt; }
-  if (kt + 1 < kt_count) { slab_step<false, false, true>(acc, fa, fb, r, ap, bp, kt & 3); ++kt; }
-  slab_step<false, false, false>(acc, fa, fb, r, ap, bp, kt & 3);
+  // two or three slabs are left (one if n_slabs is 1); s is even
+  int st = 0;
+  if (s + 2 < n_slabs) {
+    slab_step<true, true, 12, 12, 12, 12>(acc, fa, x, y, r, ap, bp, 0);
+    st = 1;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) x[h][t] = y[h][t];
+  }
+  if (n_slabs > 1) {
+    slab_step<false, true, 10, 8, 6, 4>(acc, fa, x, y, r, ap, bp, st);
+    st ^= 1;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) x[h][t] = y[h][t];
+  }
+  slab_step<false, false, 2, 0, 0, 0>(acc, fa, x, y, r, ap, bp, st);
+  if (!wm) __builtin_amdgcn_s_barrier();
 }
 
 // ---- work distribution of the row pass
 // The 256 x 256 output tiles form an (m_blocks x n_tiles) grid; it is cut into patches of pr row blocks x
-// pc column tiles: PR patch rows of QC patches ("patch steps").  The launch has G groups of pr * pc
+// pc column tiles: PR patch rows of QC patches ("patch steps").  The launch has G groups of kCells
 // workgroups; workgroup (dr, dc) of a group computes tile (row block P pr + dr, column tile Q pc + dc) of
 // every step (P, Q) its group owns, one after the other.  A group owns
 //   - base = PR / G whole patch rows (group x: rows x base .. (x+1) base - 1), swept left to right, and
@@ -217,14 +261,21 @@ __device__ __forceinline__ void tile_mainloop(f32x16 (&acc)[4][4], uint16_t *lds
 //   - Every group gets the same number of steps to within one, whatever the shape: no tail of idle
 //     compute units, and nothing depends on the row count being known on the host (a launch over a
 //     device-side row list reads its count here).
+constexpr int kCells = 32;        // workgroups of a group
+__host__ __device__ inline void patch_shape(int64_t, int &pr, int &pc) {
+  pr = 8;
+  pc = kCells / pr;
+}
 struct RowSched {
   int m_blocks, n_tiles, PR, QC, pr, pc, G;
   int base;         // whole patch rows per group
   int64_t Tr;       // steps of the remaining patch rows, shared out evenly
 };
+// pr == 0: the patch shape is the library's choice
 __device__ __forceinline__ RowSched make_sched(int64_t M, int n_tiles, int G, int pr, int pc) {
   RowSched s;
   s.m_blocks = (int)((M + FBM - 1) / FBM);
+  if (pr == 0) patch_shape(s.m_blocks, pr, pc);
   s.n_tiles = n_tiles;
   s.pr = pr; s.pc = pc; s.G = G;
   s.PR = (s.m_blocks + pr - 1) / pr;
@@ -263,42 +314,51 @@ __device__ __forceinline__ bool slot_valid(const RowSched &s, int mblock, int sl
 
 enum FusedMode { kFusedStats = 0, kFusedBwd = 1, kFusedPlanes = 2, kFusedStore = 3 };
 
+constexpr float kNoRef = -1e6f;                     // reference of an empty sum: below every real one
+
+// exponent reference of a chunk: the maximum's, rounded to an integer, so that partial sums with different
+// references combine by exact powers of two
+__device__ __forceinline__ float chunk_ref(float cm) { return (cm == neg_inf()) ? 0.f : __builtin_rintf(cm * kLog2e); }
+__device__ __forceinline__ double scale_pow2(double s, float e) { return __builtin_amdgcn_ldexp(s, (int)e); }
+
+// s (reference c) += p (reference pc); c becomes the larger one.  The references are integers: no rounding but
+// that of the fp64 add, so the result does not depend on how a row's chunks are grouped or ordered.
+__device__ __forceinline__ void add_sum(double &s, float &c, double p, float pc) {
+  const float cn = fmaxf(c, pc);
+  s = scale_pow2(s, fmaxf(c - cn, -4000.f)) + scale_pow2(p, fmaxf(pc - cn, -4000.f));
+  c = cn;
+}
+
 template <int KT, int MODE>
-__global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
-  extern __shared__ __align__(16) uint16_t lds[];
+__global__ __launch_bounds__(FTHREADS, 2) void k_fused_rows(FusedArgs a) {
+  extern __shared__ __align__(1024) uint16_t lds[];
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const int trow = tid & 255, half = tid >> 8;        // statistics: this thread's row, and which half of the columns
 
   const int64_t M = a.m_dev ? min((int64_t)*a.m_dev, a.M) : a.M;   // row count may live on the device
   const RowSched sc = make_sched(M, a.n_tiles, a.groups, a.patch_rows, a.patch_cols);
   const int grp = blockIdx.x % sc.G, cell = blockIdx.x / sc.G;       // workgroup (dr, dc) of group grp
+  if (cell >= sc.pr * sc.pc) return;
   const int dr = cell / sc.pc, dc = cell - dr * sc.pc;
   const int slot = grp * sc.pc + dc;                                  // partial-result slot of a row
   const int n_slots = sc.G * sc.pc;
   const int64_t n_steps = group_steps(sc, grp);
   const int HD = a.hidden_dim;
-  const int kt_count = HD / FBK;
   const uint16_t *__restrict__ Hp = static_cast<const uint16_t *>(a.hidden);
   const uint16_t *__restrict__ Wp = static_cast<const uint16_t *>(a.w);
 
-  // global -> LDS assignment: one wave instruction fills 16 rows x 64 bytes; wave w issues the
-  // row groups 64 w + 16 j (j = 0..3) of both operands.  Lane l lands at row l/4, 16-byte unit
-  // l%4 of its group; it fetches the unit (l%4) ^ ((row/4)%4) of that row, so that the fragment
-  // reads (32 rows at one k unit) spread over all LDS banks.
-  const int ld_row = 64 * wave + (lane >> 2);            // + 16 j
-  const int ld_unit = (lane & 3) ^ ((lane >> 4) & 3);
-  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)lds;
-  const unsigned wbase = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)wave * 4096u);
+  const LaneMap lm{wave, lane};
   // the list keeps the KT >= ktop best of the row; its last entry is the insertion threshold
   RowState<KT> st;
   const int ktop = a.ktop;
-  // Writing modes (backward, planes, store): a wave writes the rows 64 wave .. 64 wave + 63 of the tile, eight
+  // Writing modes (backward, planes, store): a wave writes the rows 32 wave .. 32 wave + 31 of the tile, eight
   // at a time; lane l then holds four consecutive columns (4 (l % 8) ..) of row 8 it + l / 8, so that the eight
   // lanes of a row write 128 contiguous bytes of an fp32 row (64 of a bf16 plane) per store instruction.  A
-  // lane therefore keeps the parameters of its eight rows (it = 0..7) for the whole patch row.
+  // lane therefore keeps the parameters of its four rows (it = 0..3) for the whole patch row.
   constexpr bool kWrites = (MODE != kFusedStats);
-  constexpr int NR = kWrites ? 8 : 1;
+  constexpr int NR = kWrites ? 4 : 1;
   float e_lse[NR], e_coef[NR];
   int e_tok[NR];
   int64_t e_base[NR];        // element offset of the row in the output (gradient rows / planes / stored rows); -1: no row
@@ -322,21 +382,48 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
         v += __shfl_xor(v, 1, kWave);
         v += __shfl_xor(v, 2, kWave);
         v += __shfl_xor(v, 4, kWave);
-        const int64_t g = row0 + wave * 64 + 8 * it + (lane >> 3);
+        const int64_t g = row0 + wave * 32 + 8 * it + (lane >> 3);
         if ((lane & 7) == 0 && g < M) a.part_s[g * n_slots + slot] = v;
       }
     } else {
-      const int64_t g = row0 + tid;
-      if (g >= M) return;
-      const int64_t pi = g * n_slots + slot;
-      a.part_m[pi] = st.m;
-      a.part_c[pi] = st.c;
-      a.part_s[pi] = st.s;
+      // the two threads of a row: the second hands its state over, the first merges and writes
+      double *x_s = reinterpret_cast<double *>(lds);
+      float *x_m = reinterpret_cast<float *>(x_s + FBM), *x_c = x_m + FBM, *x_v = x_c + FBM;
+      int *x_i = reinterpret_cast<int *>(x_v + KT * FBM);
+      __syncthreads();
+      if (half) {
+        x_s[trow] = st.s;
+        x_m[trow] = st.m;
+        x_c[trow] = st.c;
 #pragma unroll
-      for (int i = 0; i < KT; ++i) {
-        if (i < ktop) {
-          a.part_v[pi * ktop + i] = st.v[i];
-          a.part_i[pi * ktop + i] = st.id[i];
+        for (int i = 0; i < KT; ++i) {
+          x_v[i * FBM + trow] = st.v[i];
+          x_i[i * FBM + trow] = st.id[i];
+        }
+      }
+      __syncthreads();
+      if (!half) {
+        st.m = fmaxf(st.m, x_m[trow]);
+        add_sum(st.s, st.c, x_s[trow], x_c[trow]);
+#pragma unroll 1
+        for (int i = 0; i < KT; ++i) {
+          const float xv = x_v[i * FBM + trow];
+          const int xi = x_i[i * FBM + trow];
+          if (better(xv, xi, st.v[KT - 1], st.id[KT - 1])) list_insert<KT>(st.v, st.id, xv, xi);
+        }
+        const int64_t g = row0 + trow;
+        if (g < M) {
+          const int64_t pi = g * n_slots + slot;
+          a.part_m[pi] = st.m;
+          a.part_c[pi] = st.c;
+          a.part_s[pi] = st.s;
+#pragma unroll
+          for (int i = 0; i < KT; ++i) {
+            if (i < ktop) {
+              a.part_v[pi * ktop + i] = st.v[i];
+              a.part_i[pi * ktop + i] = st.id[i];
+            }
+          }
         }
       }
     }
@@ -351,7 +438,7 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
       const int mblock = P * sc.pr + dr;
       rows_live = mblock < sc.m_blocks;
       row0 = (int64_t)mblock * FBM;
-      st.m = neg_inf(); st.c = 0.f; st.s = 0.0;
+      st.m = neg_inf(); st.c = kNoRef; st.s = 0.0;
 #pragma unroll
       for (int i = 0; i < KT; ++i) { st.v[i] = neg_inf(); st.id[i] = kNoId; }
 #pragma unroll
@@ -359,15 +446,15 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
       if (rows_live) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          int64_t g = row0 + ld_row + 16 * j;
+          int64_t g = row0 + lm.a_row(j & 1) + 64 * (j >> 1);
           if (g >= M) g = M - 1;
           const int64_t hs = a.row_list ? (int64_t)a.row_list[g] : used_slot_index(g, a.rho, a.d, a.kslots);
-          a_ptr[j] = Hp + hs * HD + ld_unit * 8;
+          a_ptr[j] = Hp + hs * HD + lm.k_unit(j & 1) * 8;
         }
         if constexpr (kWrites) {
 #pragma unroll
           for (int it = 0; it < NR; ++it) {
-            const int64_t gme = row0 + wave * 64 + 8 * it + (lane >> 3);
+            const int64_t gme = row0 + wave * 32 + 8 * it + (lane >> 3);
             if (gme < M) {
               if constexpr (MODE == kFusedStore) {
                 e_base[it] = gme * a.store_pitch;
@@ -377,7 +464,7 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
                 e_lse[it] = a.lse_by_slot[a.row_list[gme]];
                 e_coef[it] = a.coef[rr];
                 e_tok[it] = a.sel_tok[(int64_t)rr * a.g + a.path_node[pidx]];
-                e_base[it] = (MODE == kFusedBwd) ? (int64_t)pidx * a.V : gme * (int64_t)a.V;
+                e_base[it] = (MODE == kFusedBwd) ? (int64_t)pidx * a.V : gme * a.plane_pitch;
               }
             }
           }
@@ -387,150 +474,103 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
     const int tile = Q * sc.pc + dc;
     if (!rows_live || tile >= sc.n_tiles) continue;     // uniform over the workgroup
     const int n0 = tile * FBN;
-    const uint16_t *b_ptr[4];
+    f32x4 acc[8][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int n = n0 + ld_row + 16 * j;
-      if (n >= a.V) n = a.V - 1;
-      b_ptr[j] = Wp + (int64_t)n * HD + ld_unit * 8;
-    }
-    f32x16 acc[4][4];
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     {
       const uint16_t *ap[4], *bp[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) { ap[j] = a_ptr[j]; bp[j] = b_ptr[j]; }
-      tile_mainloop(acc, lds, wbase, lane, wm, wn, kt_count, ap, bp);
+      for (int j = 0; j < 4; ++j) {
+        ap[j] = a_ptr[j];
+        int n = n0 + LaneMap::b_col(lm.b_row(j & 1) + 32 * (j >> 1));
+        if (n >= a.V) n = a.V - 1;
+        bp[j] = Wp + (int64_t)n * HD + lm.k_unit(j & 1) * 8;
+      }
+      tile_mainloop(acc, lds, wave, lane, HD / FBK, ap, bp);
     }
     __syncthreads();                           // all fragment reads done before the staging area is written
 
     float *stg = reinterpret_cast<float *>(lds);
     if constexpr (MODE == kFusedStats) {
-      // ---- epilogue of the statistics pass: thread t owns row t.  Four phases; phase nt takes column
-      // tile nt of both wave columns (64 columns, every wave takes part) through a column-major staging
-      // area: the four consecutive rows a lane holds of a column leave as one 16-byte write (16 writes
-      // per wave and phase, conflict-free with the column stride FSTG_CM), and a thread then reads its
-      // row with one 4-byte read per column, all 64 issued back to back.
+      // ---- epilogue of the statistics pass: threads t and t + 256 own row t.  Four phases; phase nt takes
+      // column tile nt of every wave (64 consecutive columns) through a column-major staging area: the four
+      // consecutive rows a lane holds of a column leave as one 16-byte write (8 per wave and phase,
+      // conflict-free with the column stride FSTG_CM), and a thread then reads half of its row with one 4-byte
+      // read per column, all 32 issued back to back.
       const bool full_tile = (n0 + FBN <= a.V);
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
         {
-          float *wcol = stg + (wn * 32 + (lane & 31)) * FSTG_CM + wm * 128 + 4 * (lane >> 5);
+          float *wcol = stg + (wn * 16 + (lane & 15)) * FSTG_CM + wm * 128 + 4 * (lane >> 4);
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              const f32x4 q = {acc[mt][nt][4 * g4], acc[mt][nt][4 * g4 + 1], acc[mt][nt][4 * g4 + 2],
-                               acc[mt][nt][4 * g4 + 3]};
-              *reinterpret_cast<f32x4 *>(wcol + mt * 32 + 8 * g4) = q;
-            }
-            __builtin_amdgcn_sched_barrier(0);   // 16 accumulator reads at a time keep the register pressure low
-          }
+          for (int mt = 0; mt < 8; ++mt) *reinterpret_cast<f32x4 *>(wcol + mt * 16) = acc[mt][nt];
         }
         __syncthreads();
-        // staged column c is vocabulary entry n0 + 128 (c / 32) + 32 nt + c % 32
-        const int cid0 = n0 + nt * 32;
-        float x[64];
+        const int cid0 = n0 + nt * 64 + half * 32;     // vocabulary entry of this thread's first column
+        const float *src = stg + (half * 32) * FSTG_CM + trow;
+        float x[32];
 #pragma unroll
-        for (int c = 0; c < 64; ++c) x[c] = stg[c * FSTG_CM + tid];
+        for (int c = 0; c < 32; ++c) x[c] = src[c * FSTG_CM];
         if (!full_tile) {
 #pragma unroll
-          for (int c = 0; c < 64; ++c)
-            if (cid0 + (c >> 5) * 128 + (c & 31) >= a.V) x[c] = neg_inf();     // adds nothing to max and sum
+          for (int c = 0; c < 32; ++c)
+            if (cid0 + c >= a.V) x[c] = neg_inf();     // adds nothing to max and sum
         }
-        // One pass over the 64 new logits: maximum and sum of exp2 against the reference exponent the
-        // row already has (st.c, at most 2 below its maximum in the log2 domain).  The sum is
-        // re-referenced when the maximum has moved more than that above st.c, and recomputed in the rare
-        // case that the old reference could have overflowed (or when the row has none yet).
-        const bool have_ref = (st.m != neg_inf());
-        const float c_ref = have_ref ? st.c : 0.f;
-        float cm = neg_inf(), p = 0.f;
+        // The 32 logits' maximum, then their sum of exp2 against a reference of their own: an integer, so that
+        // it joins the row's sum by an exact power of two and the result is the same for every launch geometry.
+        float cm = x[0];
 #pragma unroll
-        for (int c = 0; c < 64; ++c) {
-          cm = fmaxf(cm, x[c]);
-          p += __builtin_amdgcn_exp2f(__builtin_fmaf(x[c], kLog2e, -c_ref));
-        }
+        for (int c = 1; c < 32; ++c) cm = fmaxf(cm, x[c]);
+        const float c_ref = chunk_ref(cm);
+        float p = 0.f;
+#pragma unroll
+        for (int c = 0; c < 32; ++c) p += __builtin_amdgcn_exp2f(__builtin_fmaf(x[c], kLog2e, -c_ref));
         // top-k insertions.  Some row of the workgroup reaches its threshold in almost every phase, and
         // the other waves wait for that wave at the barrier, so the search for the candidates must not walk
-        // the 64 columns one by one: a row first marks, from registers, the columns that reach the threshold
+        // the columns one by one: a row first marks, from registers, the columns that reach the threshold
         // it had on entry (later thresholds are higher), then visits only those (typically one or two).
         if (cm >= st.v[KT - 1]) {
           const float thr = st.v[KT - 1];
-          uint32_t mask_lo = 0, mask_hi = 0;
+          uint32_t mask = 0;
 #pragma unroll
-          for (int c = 0; c < 32; ++c) {
-            mask_lo |= (x[c] >= thr) ? (1u << c) : 0u;
-            mask_hi |= (x[c + 32] >= thr) ? (1u << c) : 0u;
-          }
+          for (int c = 0; c < 32; ++c) mask |= (x[c] >= thr) ? (1u << c) : 0u;
           if (!full_tile) {      // masked columns hold -inf, which reaches the threshold of a list that is not full yet
-            const int left = a.V - cid0;                      // valid columns from cid0 on (low half), from cid0 + 128 (high half)
-            mask_lo &= (left >= 32) ? ~0u : (left <= 0 ? 0u : (1u << left) - 1u);
-            const int left_hi = left - 128;
-            mask_hi &= (left_hi >= 32) ? ~0u : (left_hi <= 0 ? 0u : (1u << left_hi) - 1u);
+            const int left = a.V - cid0;                      // valid columns from cid0 on
+            mask &= (left >= 32) ? ~0u : (left <= 0 ? 0u : (1u << left) - 1u);
           }
-          while ((mask_lo | mask_hi) != 0u) {
-            int c;
-            if (mask_lo != 0u) { c = __builtin_ctz(mask_lo); mask_lo &= mask_lo - 1u; }
-            else { c = 32 + __builtin_ctz(mask_hi); mask_hi &= mask_hi - 1u; }
-            const float xv = stg[c * FSTG_CM + tid];
-            const int xi = cid0 + (c >> 5) * 128 + (c & 31);
-            if (better(xv, xi, st.v[KT - 1], st.id[KT - 1])) list_insert<KT>(st.v, st.id, xv, xi);
+          while (mask != 0u) {
+            const int c = __builtin_ctz(mask);
+            mask &= mask - 1u;
+            const float xv = src[c * FSTG_CM];
+            if (better(xv, cid0 + c, st.v[KT - 1], st.id[KT - 1])) list_insert<KT>(st.v, st.id, xv, cid0 + c);
           }
         }
-        const float m_new = fmaxf(st.m, cm);
-        const float over = __builtin_fmaf(cm, kLog2e, -c_ref);     // how far the new maximum is above the reference
-        if (!have_ref || over > 100.f) {
-          const float c_new = (m_new == neg_inf()) ? 0.f : m_new * kLog2e;
-          float p2 = 0.f;
-#pragma unroll
-          for (int c = 0; c < 64; ++c) p2 += __builtin_amdgcn_exp2f(__builtin_fmaf(x[c], kLog2e, -c_new));
-          const double s = have_ref ? st.s * (double)__builtin_amdgcn_exp2f(st.c - c_new) : 0.0;
-          st.s = s + (double)p2;
-          st.c = c_new;
-        } else if (over > 1.f) {       // keep the dominant terms' exponents small: their rounding scales with |exponent|
-          const float c_new = m_new * kLog2e;
-          st.s = (st.s + (double)p) * (double)__builtin_amdgcn_exp2f(st.c - c_new);
-          st.c = c_new;
-        } else {
-          st.s += (double)p;
-        }
-        st.m = m_new;
+        if (cm != neg_inf()) add_sum(st.s, st.c, (double)p, c_ref);
+        st.m = fmaxf(st.m, cm);
         __syncthreads();
       }
     } else {
       // ---- epilogue of the writing modes: the same four phases and the same column-major staging; then
-      // every wave walks its 64 rows eight at a time (see the lane mapping above), two pieces of 32 columns each
+      // every wave walks its 32 rows eight at a time (see the lane mapping above), two pieces of 32 columns each
       const bool vec4 = ((a.V & 3) == 0) && (MODE != kFusedStore || (a.store_pitch & 3) == 0);
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
         {
-          float *wcol = stg + (wn * 32 + (lane & 31)) * FSTG_CM + wm * 128 + 4 * (lane >> 5);
+          float *wcol = stg + (wn * 16 + (lane & 15)) * FSTG_CM + wm * 128 + 4 * (lane >> 4);
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              const f32x4 q = {acc[mt][nt][4 * g4], acc[mt][nt][4 * g4 + 1], acc[mt][nt][4 * g4 + 2],
-                               acc[mt][nt][4 * g4 + 3]};
-              *reinterpret_cast<f32x4 *>(wcol + mt * 32 + 8 * g4) = q;
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
+          for (int mt = 0; mt < 8; ++mt) *reinterpret_cast<f32x4 *>(wcol + mt * 16) = acc[mt][nt];
         }
         __syncthreads();
 #pragma unroll
         for (int it = 0; it < NR; ++it) {
-          const float *src = stg + wave * 64 + 8 * it + (lane >> 3);
+          const float *src = stg + wave * 32 + 8 * it + (lane >> 3);
 #pragma unroll
           for (int piece = 0; piece < 2; ++piece) {
             const int c0 = piece * 32 + 4 * (lane & 7);                       // staged column of this lane's first element
-            const int col = n0 + piece * 128 + nt * 32 + 4 * (lane & 7);      // its vocabulary entry
-            if (e_base[it] < 0 || col >= a.V) continue;
+            const int col = n0 + nt * 64 + c0;                                // its vocabulary entry
+            if (e_base[it] < 0 || col >= (MODE == kFusedPlanes ? a.plane_pitch : a.V)) continue;
             float x[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = src[(c0 + e) * FSTG_CM];
@@ -569,7 +609,8 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
                     if (col + e < a.V) o[e] = gq[e];
                 }
               } else {
-                // planes: value = hi + lo in bf16 (V is a multiple of 32 in this mode: whole 8-byte stores)
+                // planes: value = hi + lo in bf16 (V is a multiple of 32 and the pitch of 64: whole 8-byte stores, zeros
+                // in the padding)
                 uint16_t hq[4], lq[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -594,8 +635,12 @@ __global__ __launch_bounds__(256) void k_fused_rows(FusedArgs a) {
   if (rows_live) flush();
 }
 
-// One wave per row: merge the partial results of the row's segments (one lane per slot) into the final
-// statistics.  Which slots hold a result follows from the launch geometry alone (slot_valid).
+// One wave per row: merge the partial results of the row's segments into the final statistics (a lane takes
+// every 64th slot).  Which slots hold a result follows from the launch geometry alone (slot_valid).
+// The k best of the slots' lists come out in k rounds of a wave-wide maximum over candidates kept in registers
+// (entries beyond kMergeReg * 64 are read again in every round): a few row blocks leave up to 512 slots a row, and
+// ranking every candidate against every other one takes (512 k)^2 steps.
+constexpr int kMergeReg = 16;
 __global__ __launch_bounds__(64) void k_fused_merge(FusedArgs a) {
   const int64_t g = blockIdx.x;
   const int64_t M = a.m_dev ? min((int64_t)*a.m_dev, a.M) : a.M;
@@ -603,86 +648,103 @@ __global__ __launch_bounds__(64) void k_fused_merge(FusedArgs a) {
   const int lane = threadIdx.x;
   const int ktop = a.ktop;
   const RowSched sc = make_sched(M, a.n_tiles, a.groups, a.patch_rows, a.patch_cols);
-  const int n_slots = sc.G * sc.pc;                       // <= 64: one lane per slot
+  const int n_slots = sc.G * sc.pc;
+  const int mblock = (int)(g / FBM);
   const int64_t oi = a.row_list ? (a.out_by_list ? g : (int64_t)a.row_list[g])
                                 : used_slot_index(g, a.rho, a.d, a.kslots);
-  __shared__ float s_v[64 * FKT];
-  __shared__ int s_i[64 * FKT];
-  __shared__ int s_claimed[FKT];
-  const bool valid = lane < n_slots && slot_valid(sc, (int)(g / FBM), lane);
-  float m = neg_inf(), c = neg_inf();
+  float m = neg_inf(), c = kNoRef;
   double s = 0.0;
-  if (valid) {
-    m = a.part_m[g * n_slots + lane];
-    if (m != neg_inf()) {
-      c = a.part_c[g * n_slots + lane];
-      s = a.part_s[g * n_slots + lane];
-    }
+  for (int q = lane; q < n_slots; q += 64) {
+    if (!slot_valid(sc, mblock, q)) continue;
+    const float pm = a.part_m[g * n_slots + q];
+    if (pm == neg_inf()) continue;
+    m = fmaxf(m, pm);
+    add_sum(s, c, a.part_s[g * n_slots + q], a.part_c[g * n_slots + q]);
   }
   const float Mx = wave_max(m);
   const float C = wave_max(c);
-  const double S = wave_sum((m == neg_inf()) ? 0.0 : s * (double)__builtin_amdgcn_exp2f(c - C));
+  const double S = wave_sum(scale_pow2(s, fmaxf(c - C, -4000.f)));
   const double lse = (double)Mx + kLn2 * (((double)C - (double)Mx * (double)kLog2e) + log2(S));
   if (lane == 0) {
     if (a.row_max) a.row_max[oi] = Mx;
     a.row_lse[oi] = (float)lse;
   }
   if (a.top_tok == nullptr) return;
-  // the valid slots' lists, packed: slot j of the packed order is the j-th valid lane
-  const uint64_t vmask = __builtin_amdgcn_ballot_w64(valid);
-  const int n_valid = __builtin_popcountll(vmask);
-  const int my_pos = __builtin_popcountll(vmask & ((1ull << lane) - 1ull));
-  if (lane < FKT) s_claimed[lane] = 0;
-  if (valid) {
-    for (int i = 0; i < ktop; ++i) {
-      s_v[my_pos * ktop + i] = a.part_v[(g * n_slots + lane) * ktop + i];
-      s_i[my_pos * ktop + i] = a.part_i[(g * n_slots + lane) * ktop + i];
-    }
+  const float *pv = a.part_v + g * n_slots * ktop;
+  const int32_t *pi = a.part_i + g * n_slots * ktop;
+  const int total = n_slots * ktop;
+  auto fetch = [&](int j, float &v, int &id) {
+    const bool ok = j < total && slot_valid(sc, mblock, j / ktop);
+    v = ok ? pv[j] : neg_inf();
+    id = ok ? pi[j] : kNoId;
+  };
+  float cv[kMergeReg];
+  int ci[kMergeReg];
+#pragma unroll
+  for (int u = 0; u < kMergeReg; ++u) {
+    cv[u] = neg_inf();
+    ci[u] = kNoId;
+    if (u * 64 < total) fetch(u * 64 + lane, cv[u], ci[u]);
   }
-  __syncthreads();
-  const int total = n_valid * ktop;
-  for (int j = lane; j < total; j += 64) {
-    const float v = s_v[j];
-    const int id = s_i[j];
-    if (id == kNoId) continue;
-    int rank = 0;
-    for (int u = 0; u < total; ++u) rank += better(s_v[u], s_i[u], v, id) ? 1 : 0;
-    if (rank < ktop) {
-      s_claimed[rank] = 1;
-      a.top_tok[oi * ktop + rank] = id;
-      if (a.top_logp) a.top_logp[oi * ktop + rank] = fminf((float)((double)v - lse), 0.f);
-      if (a.top_logit) a.top_logit[oi * ktop + rank] = v;
+  float last_v = __builtin_inff(), my_v = neg_inf();
+  int last_i = -1, my_i = kNoId;
+  for (int r = 0; r < ktop; ++r) {
+    float bv = neg_inf();
+    int bi = kNoId;
+#pragma unroll
+    for (int u = 0; u < kMergeReg; ++u) {
+      if (u * 64 < total && better(cv[u], ci[u], bv, bi)) { bv = cv[u]; bi = ci[u]; }
     }
+    for (int j = kMergeReg * 64 + lane; j < total; j += 64) {
+      float v;
+      int id;
+      fetch(j, v, id);
+      if (better(last_v, last_i, v, id) && better(v, id, bv, bi)) { bv = v; bi = id; }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const float ov = __shfl_xor(bv, off, kWave);
+      const int oid = __shfl_xor(bi, off, kWave);
+      if (better(ov, oid, bv, bi)) { bv = ov; bi = oid; }
+    }
+#pragma unroll
+    for (int u = 0; u < kMergeReg; ++u)
+      if (ci[u] == bi) { cv[u] = neg_inf(); ci[u] = kNoId; }
+    last_v = bv;
+    last_i = bi;
+    if (lane == r) { my_v = bv; my_i = bi; }
   }
-  __syncthreads();
-  // ranks no entry claimed (possible only when the row held NaNs): a valid token id with probability zero
-  if (lane < ktop && s_claimed[lane] == 0) {
-    a.top_tok[oi * ktop + lane] = lane;
-    if (a.top_logp) a.top_logp[oi * ktop + lane] = neg_inf();
-    if (a.top_logit) a.top_logit[oi * ktop + lane] = neg_inf();
+  if (lane < ktop) {
+    // ranks no entry claimed (possible only when the row held NaNs): a valid token id with probability zero
+    const bool ok = my_i != kNoId;
+    a.top_tok[oi * ktop + lane] = ok ? my_i : lane;
+    if (a.top_logp) a.top_logp[oi * ktop + lane] = ok ? fminf((float)((double)my_v - lse), 0.f) : neg_inf();
+    if (a.top_logit) a.top_logit[oi * ktop + lane] = ok ? my_v : neg_inf();
   }
 }
 
-// sum, over the valid slots of row g in slot order, of the per-segment sums of the non-token probabilities
+// sum, over the valid slots of row g, of the per-segment sums of the non-token probabilities; the same in every
+// lane of the (whole, converged) wave that calls it
 __device__ __forceinline__ double sum_others(const double *part_s, int64_t g, const RowSched &sc) {
   const int n_slots = sc.G * sc.pc;
   double tot = 0.0;
-  for (int c = 0; c < n_slots; ++c)
+  for (int c = lane_id(); c < n_slots; c += 64)
     if (slot_valid(sc, (int)(g / FBM), c)) tot += part_s[g * n_slots + c];
-  return tot;
+  return wave_sum(tot);
 }
 
-// Backward fix-up, one thread per processed row: the accepted token's entry is coef times the sum
-// of all other probabilities (summed over the vocabulary chunks in a fixed order).
-__global__ void k_fused_bwd_fixup(FusedArgs a) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Backward fix-up, one wave per processed row: the accepted token's entry is coef times the sum
+// of all other probabilities (summed in a fixed order).
+__global__ __launch_bounds__(64) void k_fused_bwd_fixup(FusedArgs a) {
+  const int64_t g = blockIdx.x;
   const int64_t M = a.m_dev ? min((int64_t)*a.m_dev, a.M) : a.M;
   if (g >= M) return;
   const double tot = sum_others(a.part_s, g, make_sched(M, a.n_tiles, a.groups, a.patch_rows, a.patch_cols));
   const int pidx = a.list_p[g];
   const int rr = pidx / a.d;
   const int tok = a.sel_tok[(int64_t)rr * a.g + a.path_node[pidx]];
-  if (tok >= 0 && tok < a.V) a.grad_rows[(int64_t)pidx * a.V + tok] = (float)((double)a.coef[rr] * tot);
+  if (threadIdx.x == 0 && tok >= 0 && tok < a.V)
+    a.grad_rows[(int64_t)pidx * a.V + tok] = (float)((double)a.coef[rr] * tot);
 }
 
 // Ordered compaction (single workgroup): the (root, step) pairs that carry a gradient, their
@@ -793,69 +855,69 @@ __global__ __launch_bounds__(64) void k_gather_dot(GatherDotArgs a) {
 // Hidden-state gradient, one 256 (rows of the list) x 256 (hidden columns) tile per workgroup and split of
 // the contraction: partial[split] = sum over the split's k slabs of G . W, G = [plane_hi | plane_lo]
 // (contraction length 2 V), W hidden-major so that both operands are contiguous along the vocabulary.
-__global__ __launch_bounds__(256) void k_fused_dh(FusedDhArgs a) {
-  extern __shared__ __align__(16) uint16_t lds[];
+__global__ __launch_bounds__(FTHREADS, 2) void k_fused_dh(FusedDhArgs a) {
+  extern __shared__ __align__(1024) uint16_t lds[];
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
   const int split = blockIdx.x % a.n_splits;
   const int rest = blockIdx.x / a.n_splits;
   const int hblock = rest % a.h_blocks, mblock = rest / a.h_blocks;
   const int64_t M = min((int64_t)*a.m_dev, a.M);
   const int64_t row0 = (int64_t)mblock * FBM;
   if (row0 >= M) return;
-  const int nks = a.V / FBK;                                  // slabs per plane
+  const int nks = (int)(a.plane_pitch / FBK);                 // slabs per plane (the last one may be half padding)
   const int s0 = split * a.slabs_per_split;
-  const int kt_count = min(a.slabs_per_split, 2 * nks - s0);  // >= 1 by the launch geometry
+  const int s1 = min(s0 + a.slabs_per_split, 2 * nks);
   const int h0 = hblock * FBN;
-  const int ld_row = 64 * wave + (lane >> 2);
-  const int ld_unit = (lane & 3) ^ ((lane >> 4) & 3);
-  const uint16_t *a_hi[4], *a_lo[4], *b_ptr[4];
+  const LaneMap lm{wave, lane};
+  int64_t a_off[4];
+  const uint16_t *b_ptr[4];
   const uint16_t *Wp = static_cast<const uint16_t *>(a.w_hv);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    int64_t g = row0 + ld_row + 16 * j;
+    int64_t g = row0 + lm.a_row(j & 1) + 64 * (j >> 1);
     if (g >= M) g = M - 1;
-    a_hi[j] = a.plane_hi + g * a.V + ld_unit * 8;
-    a_lo[j] = a.plane_lo + g * a.V + ld_unit * 8;
-    int n = h0 + ld_row + 16 * j;
+    a_off[j] = g * a.plane_pitch + lm.k_unit(j & 1) * 8;
+    int n = h0 + LaneMap::b_col(lm.b_row(j & 1) + 32 * (j >> 1));
     if (n >= a.hidden_dim) n = a.hidden_dim - 1;
-    b_ptr[j] = Wp + (int64_t)n * a.V + ld_unit * 8;
+    b_ptr[j] = Wp + (int64_t)n * a.V + lm.k_unit(j & 1) * 8;
   }
-  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)lds;
-  const unsigned wbase = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)wave * 4096u);
-  f32x16 acc[4][4];
+  f32x4 acc[8][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  // the split's slabs [s0, s0 + kt_count) of the contraction over [hi plane | lo plane]: the part inside the
-  // hi plane, then the part inside the lo plane, each a contiguous k range of both operands
-  const int n_hi = max(0, min(s0 + kt_count, nks) - s0);
-  if (n_hi > 0) {
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // The split's slabs [s0, s1) of the contraction over [hi plane | lo plane], in up to four contiguous k ranges of
+  // both operands: whole slabs of the hi plane, its last slab if that is half padding, and the same of the lo
+  // plane.  In a half slab the head's rows end in the middle: the lanes beyond fetch the slab's first half again,
+  // which the planes' zeros take out of the sum.
+  const int whole = a.V / FBK;
+#pragma unroll 1
+  for (int part = 0; part < 4; ++part) {
+    const int base = (part >> 1) * nks;
+    const bool tail = part & 1;
+    const int lo = max(s0, base + (tail ? whole : 0)), hi = min(s1, base + (tail ? nks : whole));
+    if (lo >= hi) continue;
+    const uint16_t *plane = (part >> 1) ? a.plane_lo : a.plane_hi;
+    const int64_t k0 = (int64_t)(lo - base) * FBK;
     const uint16_t *ap[4], *bp[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { ap[j] = a_hi[j] + (int64_t)s0 * FBK; bp[j] = b_ptr[j] + (int64_t)s0 * FBK; }
-    tile_mainloop(acc, lds, wbase, lane, wm, wn, n_hi, ap, bp);
-  }
-  if (kt_count - n_hi > 0) {
-    const int l0 = max(s0, nks) - nks;
-    const uint16_t *ap[4], *bp[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { ap[j] = a_lo[j] + (int64_t)l0 * FBK; bp[j] = b_ptr[j] + (int64_t)l0 * FBK; }
-    tile_mainloop(acc, lds, wbase, lane, wm, wn, kt_count - n_hi, ap, bp);
+    for (int j = 0; j < 4; ++j) {
+      ap[j] = plane + a_off[j] + k0;
+      bp[j] = b_ptr[j] + k0 - ((tail && lm.k_unit(j & 1) >= 4) ? FBK / 2 : 0);
+    }
+    tile_mainloop(acc, lds, wave, lane, hi - lo, ap, bp);
   }
   float *out = a.partial + (int64_t)split * a.M * a.hidden_dim;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t row = row0 + wm * 128 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        const int col = h0 + wn * 128 + j * 32 + (lane & 31);
+      for (int e = 0; e < 4; ++e) {
+        const int64_t row = row0 + wm * 128 + i * 16 + 4 * (lane >> 4) + e;
+        const int col = h0 + j * 64 + wn * 16 + (lane & 15);
         if (row < M && col < a.hidden_dim) out[row * a.hidden_dim + col] = acc[i][j][e];
       }
 }
@@ -887,7 +949,17 @@ static void set_lds_attr(K kern) {
                             (int)kFusedLdsBytes);
 }
 
-static int fused_grid(const FusedArgs &a) { return a.groups * a.patch_rows * a.patch_cols; }
+int64_t fused_partials(int64_t rows, int groups, int pr, int pc) {
+  if (pr != 0) return rows * groups * pc;
+  int64_t most = 0;
+  for (int64_t mb = 1; mb <= 64 && (mb - 1) * FBM < rows; ++mb) {      // from 19 row blocks on the patch is 4 wide
+    patch_shape(mb, pr, pc);
+    most = std::max(most, std::min(rows, mb * FBM) * pc);
+  }
+  return groups * std::max(most, rows * 4);
+}
+
+static int fused_grid(const FusedArgs &a) { return a.groups * kCells; }
 
 // the kernels that use the whole slab ring need the dynamic LDS limit raised once per process
 // (initialisation of a function-local static is thread-safe)
@@ -909,27 +981,27 @@ void launch_fused_rows(const FusedArgs &a, hipStream_t st) {
   ensure_lds_attrs();
   const int blocks = fused_grid(a);
   if (a.store_rows != nullptr)
-    hipLaunchKernelGGL((k_fused_rows<1, kFusedStore>), dim3(blocks), dim3(256), kFusedLdsBytes, st, a);
+    hipLaunchKernelGGL((k_fused_rows<1, kFusedStore>), dim3(blocks), dim3(FTHREADS), kFusedLdsBytes, st, a);
   else if (a.plane_hi != nullptr)
-    hipLaunchKernelGGL((k_fused_rows<1, kFusedPlanes>), dim3(blocks), dim3(256), kFusedLdsBytes, st, a);
+    hipLaunchKernelGGL((k_fused_rows<1, kFusedPlanes>), dim3(blocks), dim3(FTHREADS), kFusedLdsBytes, st, a);
   else if (a.grad_rows != nullptr)
-    hipLaunchKernelGGL((k_fused_rows<1, kFusedBwd>), dim3(blocks), dim3(256), kFusedLdsBytes, st, a);
+    hipLaunchKernelGGL((k_fused_rows<1, kFusedBwd>), dim3(blocks), dim3(FTHREADS), kFusedLdsBytes, st, a);
   else if (a.ktop <= 1)
-    hipLaunchKernelGGL((k_fused_rows<1, kFusedStats>), dim3(blocks), dim3(256), kFusedLdsBytes, st, a);
+    hipLaunchKernelGGL((k_fused_rows<1, kFusedStats>), dim3(blocks), dim3(FTHREADS), kFusedLdsBytes, st, a);
   else if (a.ktop <= 8)
-    hipLaunchKernelGGL((k_fused_rows<8, kFusedStats>), dim3(blocks), dim3(256), kFusedLdsBytes, st, a);
+    hipLaunchKernelGGL((k_fused_rows<8, kFusedStats>), dim3(blocks), dim3(FTHREADS), kFusedLdsBytes, st, a);
   else
-    hipLaunchKernelGGL((k_fused_rows<16, kFusedStats>), dim3(blocks), dim3(256), kFusedLdsBytes, st, a);
+    hipLaunchKernelGGL((k_fused_rows<16, kFusedStats>), dim3(blocks), dim3(FTHREADS), kFusedLdsBytes, st, a);
 }
 
 void launch_fused_dh(const FusedDhArgs &a, hipStream_t st) {
   ensure_lds_attrs();
-  hipLaunchKernelGGL(k_fused_dh, dim3((unsigned)(a.m_blocks * a.h_blocks * a.n_splits)), dim3(256), kFusedLdsBytes, st, a);
+  hipLaunchKernelGGL(k_fused_dh, dim3((unsigned)(a.m_blocks * a.h_blocks * a.n_splits)), dim3(FTHREADS), kFusedLdsBytes, st, a);
   hipLaunchKernelGGL(k_fused_dh_reduce, dim3((unsigned)a.M), dim3(256), 0, st, a);
 }
 
 void launch_fused_bwd_fixup(const FusedArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL(k_fused_bwd_fixup, dim3((unsigned)((a.M + 255) / 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_fused_bwd_fixup, dim3((unsigned)a.M), dim3(64), 0, st, a);
 }
 
 void launch_bwd_rows(const BwdRowsArgs &a, hipStream_t st) {

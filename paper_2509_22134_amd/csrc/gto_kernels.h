@@ -92,8 +92,9 @@ struct FusedArgs {
   const int32_t *row_list;   // optional: slot index of each processed row
   int out_by_list;           // with row_list: statistics are written at the list position, not at the slot
   int n_tiles;               // column tiles of 256 tokens
-  int groups, patch_rows, patch_cols;   // launch geometry: groups x (patch_rows x patch_cols) workgroups;
-                             // n_slots = groups * patch_cols partial results per row (<= 64)
+  int groups, patch_rows, patch_cols;   // launch geometry: groups of 32 workgroups as patch_rows x patch_cols
+                             // (patch_rows 0: chosen from the row count where it is known, on the device);
+                             // n_slots = groups * patch columns partial results per row
   float *part_m, *part_c;    // [M, n_slots]
   double *part_s;            // [M, n_slots]
   float *part_v;             // [M, n_slots, ktop]
@@ -110,6 +111,7 @@ struct FusedArgs {
   // into two bf16 planes [M, V] (value = hi + lo; zero at the accepted token), the row operand of the
   // hidden-state gradient; part_s receives the sum of the other probabilities as in the backward mode
   uint16_t *plane_hi, *plane_lo;
+  int64_t plane_pitch;       // elements between rows of a plane: V rounded up to a multiple of 64, padded with zeros
   // store mode (store_rows != null): the fp32 logits of row i of the processed rows go to store_rows[i, :V]
   float *store_rows;
   int64_t store_pitch;
@@ -117,7 +119,8 @@ struct FusedArgs {
 
 // Hidden-state gradient dH = G . W of the fused variant: G = the two bf16 planes, W hidden-major.
 struct FusedDhArgs {
-  const uint16_t *plane_hi, *plane_lo;   // [M, V]
+  const uint16_t *plane_hi, *plane_lo;   // [M, plane_pitch]
+  int64_t plane_pitch;
   const void *w_hv;          // bf16 [hidden_dim, V]
   const void *w_vh;          // bf16 [V, hidden_dim] (row of the accepted token, added exactly)
   int hidden_dim, V, d, g;
@@ -155,6 +158,8 @@ struct PairArgs {
   int64_t *slot;
   int32_t *tok;
 };
+// partial results (of one row and slot each) that a row pass over at most `rows` rows may leave
+int64_t fused_partials(int64_t rows, int groups, int patch_rows, int patch_cols);
 void launch_pairs(const PairArgs &a, int mode, hipStream_t st);
 void launch_fused_rows(const FusedArgs &a, hipStream_t st);
 void launch_fused_bwd_fixup(const FusedArgs &a, hipStream_t st);

@@ -302,3 +302,40 @@ def test_fused_zero_fill(gpu_device):
     v = a.grad_slot >= 0
     assert torch.equal(a.grad_slot, b.grad_slot) and torch.equal(a.grad_rows[v], b.grad_rows[v])
     assert not b.grad_rows[~v].any() and bool((a.grad_rows[~v] == 7.0).all())
+
+
+@pytest.mark.parametrize("R,hidden,V,k", [
+    (51, 64, 1000, 4),       # one k slab; 255 rows, ragged vocabulary tail
+    (52, 128, 1288, 8),      # two slabs; 260 rows: a row block of four
+    (13, 192, 264, 16),      # three slabs; a vocabulary tile of eight columns, the longest list
+    (7, 256, 776, 4),        # four slabs: one trip of the paired loop
+    (103, 320, 2056, 8),     # five
+])
+def test_fused_row_statistics_main_loop_edges(gpu_device, R, hidden, V, k):
+    """Few k slabs (the main loop's start and end) and ragged row and column tiles.  Hidden states and heads are small
+    integers, so every product and sum is exact in fp32 and ids are compared exactly, the many ties included; the
+    log-sum-exp is a sum of at most V fp32 terms of one ulp each, summed in fp64 per 32 of them."""
+    gen = torch.Generator().manual_seed(1000 + hidden)
+    d = 2
+    H = torch.randint(-2, 3, (R, d, k, hidden), generator=gen).to(torch.bfloat16).to(gpu_device)
+    W = (torch.randint(-2, 3, (V, hidden), generator=gen).float() / 8).to(torch.bfloat16).to(gpu_device)
+    cfg = G.make_config(R=R, d=d, k=k, g=4, V=V, dtype=torch.bfloat16)
+    ws = torch.empty(G.gto_fused_workspace_bytes(cfg, hidden), dtype=torch.uint8, device=gpu_device)
+    ds, ts = U.alloc_poisoned(G.alloc_draft_stats, cfg, gpu_device), U.alloc_poisoned(G.alloc_target_stats, cfg, gpu_device)
+    G.gto_fused_draft_row_stats(cfg, H, W, ds, ws)
+    G.gto_fused_target_row_stats(cfg, H, W, ts, ws)
+    torch.cuda.synchronize()
+    L = O.fused_logits(H.float().cpu().numpy(), W.float().cpu().numpy())
+    od, ot = O.draft_row_stats(L, k), O.target_row_stats(L)
+    gd, gt = U.to_np(ds), U.to_np(ts)
+    m = U.used_mask(R, d, k)
+    assert np.array_equal(gd["top_tok"][m], od["top_tok"][m])
+    assert np.array_equal(gt["t_argmax"][m], ot["t_argmax"][m])
+    assert np.array_equal(gd["row_max"][m], od["row_max"][m].astype(np.float32))
+    np.testing.assert_allclose(gd["row_lse"][m], od["row_lse"][m], rtol=1e-6, atol=1e-6)
+    np.testing.assert_allclose(gt["t_lse"][m], ot["t_lse"][m], rtol=1e-6, atol=1e-6)
+
+
+def test_fused_hidden_state_gradient_half_slab(gpu_device):
+    """A vocabulary that is an odd multiple of 32: the contraction's last k slab of each plane is half padding."""
+    test_fused_hidden_state_gradient(gpu_device, 40, 3, 8, 20, 256, 2080, 0)
