@@ -93,8 +93,8 @@ typedef struct gto_config {
   int32_t fused_groups;   /* fused variant: groups of workgroups the row pass is launched with, 0 (= 8: one
                              group per XCD, one workgroup per compute unit) .. 16 (8 with fused_layout 1);
                              else GTO_E_MODE.  Sizes the fused workspace.                          */
-  int32_t fused_layout;   /* fused variant: a group is 0 = 8 row blocks x 4 column tiles of workgroups
-                             (the library's choice), 1 = 4 x 8                                     */
+  int32_t fused_layout;   /* fused variant: the 32 workgroups of a group as row blocks x column tiles: 0 = the
+                             library's choice (8 x 4 for many rows, flatter for few), 1 = 4 x 8     */
   int32_t reserved;       /* must be 0                                                          */
 } gto_config;
 

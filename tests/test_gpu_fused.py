@@ -339,3 +339,32 @@ def test_fused_row_statistics_main_loop_edges(gpu_device, R, hidden, V, k):
 def test_fused_hidden_state_gradient_half_slab(gpu_device):
     """A vocabulary that is an odd multiple of 32: the contraction's last k slab of each plane is half padding."""
     test_fused_hidden_state_gradient(gpu_device, 40, 3, 8, 20, 256, 2080, 0)
+
+
+@pytest.mark.parametrize("R", [3, 60, 140, 230, 450, 500, 860])     # 1, 2, 3, 5, 9, 10 and 17 row blocks
+def test_fused_patch_shape_follows_the_row_count(gpu_device, R):
+    """The launch geometry the library picks for a row count against the fixed 4 x 8 patch, on every row and on a
+    compacted row list whose length is only known on the device; nothing behind the stated workspace is touched."""
+    d, k, hidden, V = 2, 4, 64, 2312
+    gen = torch.Generator().manual_seed(77 + R)
+    H = torch.randn((R, d, k, hidden), generator=gen).to(torch.bfloat16).to(gpu_device)
+    W = (torch.randn((V, hidden), generator=gen) * 0.5).to(torch.bfloat16).to(gpu_device)
+    res = []
+    for layout in (0, 1):
+        cfg = G.make_config(R=R, d=d, k=k, g=9, V=V, dtype=torch.bfloat16, fused_layout=layout,
+                            flags=G.GTO_FLAG_TARGET_PRUNE)
+        need = G.gto_fused_workspace_bytes(cfg, hidden)
+        ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=gpu_device)
+        b = dict(ds=G.alloc_draft_stats(cfg, gpu_device), pool=G.alloc_pool(cfg, gpu_device),
+                 tree=G.alloc_tree(cfg, gpu_device), ts=G.alloc_target_stats(cfg, gpu_device),
+                 rew=G.alloc_reward(cfg, gpu_device))
+        G.gto_expand_tree_fused(cfg, H, W, b["ds"], b["pool"], ws[:need])
+        G.gto_select_topg(cfg, b["pool"], b["tree"])
+        G.gto_tree_reward_fused(cfg, b["tree"], H, W.flip(0).contiguous(), b["ts"], b["rew"], ws[:need])
+        torch.cuda.synchronize()
+        assert bool((ws[need:] == 0x5A).all())
+        res.append(b)
+    for grp in res[0]:
+        for n, x in res[0][grp].items():
+            # partial sums combine by exact powers of two in fp64, so the geometry leaves fp32 results alone
+            assert torch.equal(x, res[1][grp][n]), (grp, n)
