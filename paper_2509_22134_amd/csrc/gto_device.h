@@ -61,6 +61,60 @@ __device__ __forceinline__ uint32_t ordered_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+__device__ __forceinline__ float from_ordered_bits(uint32_t o) {
+  return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
+}
+
+// Packed ranking key: (score descending, index ascending) is descending key order.  Keys are unique and never 0.
+__device__ __forceinline__ uint64_t rank_key(float score, int index) {
+  return ((uint64_t)ordered_bits(score) << 32) | (uint32_t)(0xffffffffu - (uint32_t)index);
+}
+__device__ __forceinline__ float key_score(uint64_t key) { return from_ordered_bits((uint32_t)(key >> 32)); }
+__device__ __forceinline__ int key_index(uint64_t key) { return (int)(0xffffffffu - (uint32_t)key); }
+
+// s * 2^e for an integer-valued e (far below the exponent range: zero); exact but for underflow.
+__device__ __forceinline__ double scale_pow2(double s, float e) { return __builtin_amdgcn_ldexp(s, (int)fmaxf(e, -4000.f)); }
+
+// Number of set lanes below this one.
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Wave reductions in DPP moves (rows of 16, then across rows): the result is the same in every lane.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v, float fill) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(fill), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {      // lanes without a source receive 0
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  const float f = neg_inf();
+  v = fmaxf(v, dpp<kRowShr + 1>(v, f));
+  v = fmaxf(v, dpp<kRowShr + 2>(v, f));
+  v = fmaxf(v, dpp<kRowShr + 4>(v, f));
+  v = fmaxf(v, dpp<kRowShr + 8>(v, f));
+  v = fmaxf(v, dpp<kRowBcast15>(v, f));
+  v = fmaxf(v, dpp<kRowBcast31>(v, f));
+  return readlane(v, 63);
+}
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  v += dpp<kRowShr + 1>(v);
+  v += dpp<kRowShr + 2>(v);
+  v += dpp<kRowShr + 4>(v);
+  v += dpp<kRowShr + 8>(v);
+  v += dpp<kRowBcast15>(v);
+  v += dpp<kRowBcast31>(v);
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, 63), hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
 // 16 bytes of logits -> fp32 values.
 template <typename T> struct Elem;
 template <> struct Elem<uint16_t> {           // bf16 storage

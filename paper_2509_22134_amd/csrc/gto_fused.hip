@@ -320,18 +320,17 @@ __device__ __forceinline__ bool slot_valid(const RowSched &s, int mblock, int sl
 
 enum FusedMode { kFusedStats = 0, kFusedBwd = 1, kFusedPlanes = 2, kFusedStore = 3 };
 
-constexpr float kNoRef = -1e6f;                     // reference of an empty sum: below every real one
+constexpr float kNoRef = -3.402823466e+38f;         // reference of an empty sum: below every real one
 
 // exponent reference of a chunk: the maximum's, rounded to an integer, so that partial sums with different
 // references combine by exact powers of two
 __device__ __forceinline__ float chunk_ref(float cm) { return (cm == neg_inf()) ? 0.f : __builtin_rintf(cm * kLog2e); }
-__device__ __forceinline__ double scale_pow2(double s, float e) { return __builtin_amdgcn_ldexp(s, (int)e); }
 
 // s (reference c) += p (reference pc); c becomes the larger one.  The references are integers: no rounding but
 // that of the fp64 add, so the result does not depend on how a row's chunks are grouped or ordered.
 __device__ __forceinline__ void add_sum(double &s, float &c, double p, float pc) {
   const float cn = fmaxf(c, pc);
-  s = scale_pow2(s, fmaxf(c - cn, -4000.f)) + scale_pow2(p, fmaxf(pc - cn, -4000.f));
+  s = scale_pow2(s, c - cn) + scale_pow2(p, pc - cn);
   c = cn;
 }
 
@@ -669,7 +668,7 @@ __global__ __launch_bounds__(64) void k_fused_merge(FusedArgs a) {
   }
   const float Mx = wave_max(m);
   const float C = wave_max(c);
-  const double S = wave_sum(scale_pow2(s, fmaxf(c - C, -4000.f)));
+  const double S = wave_sum(scale_pow2(s, c - C));
   const double lse = (double)Mx + kLn2 * (((double)C - (double)Mx * (double)kLog2e) + log2(S));
   if (lane == 0) {
     if (a.row_max) a.row_max[oi] = Mx;

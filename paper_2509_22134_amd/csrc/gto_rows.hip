@@ -10,6 +10,8 @@
 // Both are HBM-bandwidth bound by design: per element they spend one conversion, one fused
 // multiply-add, one exp2 and one add; the top-k costs one max per element plus a rarely
 // taken insertion path.
+#include <type_traits>
+
 #include "gto_device.h"
 #include "gto_kernels.h"
 
@@ -34,28 +36,44 @@ struct TopList {
   }
 };
 
-// k-th largest of the 64 per-lane values (k <= 64), the same in every lane.
+// k-th largest of the 64 lanes' values (k <= 64), the same in every lane: its ordered bits are built from the top,
+// one compare and one scalar bit count per bit (BITS = 16 is exact for values that bf16 holds).
+template <int BITS>
 __device__ __forceinline__ float kth_largest_of_lanes(float x, int k) {
-  int cnt = 0;
+  const uint32_t o = ordered_bits(x);
+  uint32_t t = 0;
 #pragma unroll
-  for (int i = 0; i < kWave; ++i) cnt += (readlane(x, i) > x) ? 1 : 0;
-  float cand = (cnt < k) ? x : __builtin_inff();
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) cand = fminf(cand, __shfl_xor(cand, off, kWave));
-  return cand;
+  for (int b = 31; b > 31 - BITS; --b) {
+    const uint32_t cand = t | (1u << b);
+    if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(o >= cand)) >= k) t = cand;
+  }
+  // the low bits of a negative number's image are set
+  if (BITS < 32 && (t & 0x80000000u) == 0u) t |= (1u << (32 - BITS)) - 1u;
+  return from_ordered_bits(t);
 }
 
-// Per-lane streaming state: running max m, log2-domain offset c = m*log2(e) and
-// s = sum 2^(x*log2(e) - c) over the elements this lane has seen.  Each 16-byte vector is summed
-// in fp32 and then added to s in fp64 (a full-rate add on this chip): an fp32 running sum that
-// already holds a dominant term would silently drop the many tiny ones added after it.
-struct LaneAcc {
+// Streaming state of a wave: c, the log2-domain reference exponent all its lanes share, and per lane the running
+// maximum m and s = sum 2^(x*log2(e) - c) over the elements the lane has seen.  c is an integer near the wave's
+// maximum: it moves, rarely, when a tile exceeds it by more than 1 (exponents of the dominant terms stay small, whose
+// rounding scales with them), and moving it scales s by an exact power of two.  A tile is summed in fp32 and then
+// added to s in fp64: an fp32 running sum that already holds a dominant term would silently drop the many tiny ones
+// added after it.  (A reference per lane instead costs an exp2 and fp64 products in every tile, fp64 adds per vector
+// rather than per tile as much again: together a tenth of the loop's issue slots.)
+struct WaveAcc {
   float m, c;
   double s;
-  __device__ __forceinline__ void init() { m = neg_inf(); c = 0.f; s = 0.0; }
+  __device__ __forceinline__ void init() { m = neg_inf(); c = -3.402823466e+38f; s = 0.0; }
+  __device__ __forceinline__ void refer(float cm) {
+    if (__builtin_amdgcn_ballot_w64(__builtin_fmaf(cm, kLog2e, -c) > 1.f) == 0ull) return;
+    const float cn = __builtin_rintf(wave_max_dpp(cm) * kLog2e);
+    s = scale_pow2(s, c - cn);
+    c = cn;
+  }
 };
 
-enum RowMode { kDraftTopK = 0, kTargetArgmax = 1, kLseOnly = 2 };
+// kDraftTopK: top-k collected at the end of the row (see LaneTop).  kDraftInsert: top-k kept in a sorted list while
+// streaming (large k, or a row with more groups than LaneTop can number).
+enum RowMode { kDraftTopK = 0, kTargetArgmax = 1, kLseOnly = 2, kDraftInsert = 3 };
 
 // Issues the LOADS 16-byte loads of one tile (lane l, load u: elements (u*64 + l)*EPV ...).
 template <typename T, int LOADS, bool GUARD>
@@ -67,103 +85,287 @@ __device__ __forceinline__ void load_tile(const T *__restrict__ row, int tile_ba
     if (!GUARD || e0 < V) {
       q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row + e0));
     } else {
-      q[u] = u32x4{0u, 0u, 0u, 0u};
+      const uint32_t none = (sizeof(T) == 2) ? 0xff80ff80u : 0xff800000u;      // -inf
+      q[u] = u32x4{none, none, none, none};
     }
   }
 }
 
-template <typename T, int LOADS, bool GUARD, int MODE>
-__device__ __forceinline__ void scan_tile(const u32x4 *q, int tile_base, int V, int lane,
-                                          int ktop_rt, bool &first, LaneAcc &acc, TopList &top,
-                                          float &thr_v, int &thr_i) {
-  const int ktop = (MODE == kTargetArgmax) ? 1 : ktop_rt;
-  constexpr int EPV = Elem<T>::kPerVec;
-  float x[LOADS][EPV];
+// One tile as fp32 (entries beyond V: -inf) and its per-vector maxima.
+template <typename T, int LOADS>
+struct Tile {
+  static constexpr int EPV = Elem<T>::kPerVec;
+  float x[LOADS][EPV], mu[LOADS];
+  template <bool GUARD>
+  __device__ __forceinline__ void unpack(const u32x4 *q, int tile_base, int V, int lane) {
 #pragma unroll
-  for (int u = 0; u < LOADS; ++u) {
-    Elem<T>::unpack(q[u], x[u]);
-    if (GUARD) {
-      const int e0 = tile_base + (u * kWave + lane) * EPV;
+    for (int u = 0; u < LOADS; ++u) {
+      Elem<T>::unpack(q[u], x[u]);
+      if (GUARD && V % EPV != 0) {             // the last vector is partly padding
+        const int e0 = tile_base + (u * kWave + lane) * EPV;
 #pragma unroll
-      for (int e = 0; e < EPV; ++e)
-        if (e0 + e >= V) x[u][e] = neg_inf();
+        for (int e = 0; e < EPV; ++e)
+          if (e0 + e >= V) x[u][e] = neg_inf();
+      }
+      mu[u] = x[u][0];
+#pragma unroll
+      for (int e = 1; e < EPV; ++e) mu[u] = fmaxf(mu[u], x[u][e]);
     }
   }
-  float mu[LOADS];
-#pragma unroll
-  for (int u = 0; u < LOADS; ++u) {
-    mu[u] = x[u][0];
-#pragma unroll
-    for (int e = 1; e < EPV; ++e) mu[u] = fmaxf(mu[u], x[u][e]);
+  __device__ __forceinline__ float max_of(int u0, int n) const {
+    float m = mu[u0];
+    for (int u = 1; u < n; ++u) m = fmaxf(m, mu[u0 + u]);
+    return m;
   }
-  float cm = mu[0];
+  // cm: the lane's maximum of the tile
+  __device__ __forceinline__ void accumulate(WaveAcc &acc, float cm) const {
+    acc.refer(cm);
+    float p[LOADS];
 #pragma unroll
-  for (int u = 1; u < LOADS; ++u) cm = fmaxf(cm, mu[u]);
-
-  // online log-sum-exp in the log2 domain
-  const float m_new = fmaxf(acc.m, cm);
-  const float c_new = (m_new == neg_inf()) ? 0.f : m_new * kLog2e;
-  const float scale = __builtin_amdgcn_exp2f(acc.c - c_new);
-  double s = (acc.m == neg_inf()) ? 0.0 : acc.s * (double)scale;
+    for (int u = 0; u < LOADS; ++u) {
+      p[u] = 0.f;
 #pragma unroll
-  for (int u = 0; u < LOADS; ++u) {
-    float p = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPV; ++e) p += __builtin_amdgcn_exp2f(__builtin_fmaf(x[u][e], kLog2e, -c_new));
-    s += (double)p;
+      for (int e = 0; e < EPV; ++e) p[u] += __builtin_amdgcn_exp2f(__builtin_fmaf(x[u][e], kLog2e, -acc.c));
+    }
+    static_assert(LOADS == 4, "sum of the vectors");
+    acc.s += (double)((p[0] + p[1]) + (p[2] + p[3]));
+    acc.m = fmaxf(acc.m, cm);
   }
-  acc.m = m_new;
-  acc.c = c_new;
-  acc.s = s;
-
-  if (MODE == kLseOnly) return;
-  // top-k: first tile of a wave seeds the threshold with the k-th largest lane maximum, a
-  // value that at least k elements of this tile reach.
-  if (first) {
-    first = false;
-    thr_v = kth_largest_of_lanes(cm, ktop);
-    thr_i = kNoId;
-  }
-  const int lane_first = tile_base + lane * EPV;
-  const bool hit = better(cm, lane_first, thr_v, thr_i);
-  if (__builtin_amdgcn_ballot_w64(hit) == 0) return;
-
+  // inserts what beats the threshold (the k-th entry of the list, or a lower bound of it)
+  template <bool GUARD>
+  __device__ __forceinline__ void insert(int tile_base, int V, int lane, int ktop, TopList &top, float &thr_v, int &thr_i) const {
+    const int lane_first = tile_base + lane * EPV;
+    if (__builtin_amdgcn_ballot_w64(better(max_of(0, LOADS), lane_first, thr_v, thr_i)) == 0) return;
 #pragma unroll
-  for (int u = 0; u < LOADS; ++u) {
-    // skip a whole vector position when no lane's vector maximum can enter the list
-    if (__builtin_amdgcn_ballot_w64(better(mu[u], tile_base + (u * kWave + lane) * EPV, thr_v, thr_i)) == 0)
-      continue;
+    for (int u = 0; u < LOADS; ++u) {
+      // skip a whole vector position when no lane's vector maximum can enter the list
+      if (__builtin_amdgcn_ballot_w64(better(mu[u], tile_base + (u * kWave + lane) * EPV, thr_v, thr_i)) == 0) continue;
 #pragma unroll
-    for (int e = 0; e < EPV; ++e) {
-      const int my_id = tile_base + (u * kWave + lane) * EPV + e;
-      bool p = better(x[u][e], my_id, thr_v, thr_i);
-      if (GUARD) p = p && (my_id < V);
-      uint64_t mask = __builtin_amdgcn_ballot_w64(p);
-      while (mask) {
-        const int src = __builtin_ctzll(mask);
-        mask &= mask - 1;
-        const float cv = readlane(x[u][e], src);
-        const int ci = tile_base + (u * kWave + src) * EPV + e;
-        if (better(cv, ci, thr_v, thr_i)) {
-          top.insert(cv, ci);
-          const float nv = readlane(top.v, ktop - 1);
-          const int ni = readlane(top.id, ktop - 1);
-          if (better(nv, ni, thr_v, thr_i)) {
-            thr_v = nv;
-            thr_i = ni;
+      for (int e = 0; e < EPV; ++e) {
+        const int my_id = tile_base + (u * kWave + lane) * EPV + e;
+        bool p = better(x[u][e], my_id, thr_v, thr_i);
+        if (GUARD) p = p && (my_id < V);
+        uint64_t mask = __builtin_amdgcn_ballot_w64(p);
+        while (mask) {
+          const int src = __builtin_ctzll(mask);
+          mask &= mask - 1;
+          const float cv = readlane(x[u][e], src);
+          const int ci = tile_base + (u * kWave + src) * EPV + e;
+          if (better(cv, ci, thr_v, thr_i)) {
+            top.insert(cv, ci);
+            const float nv = readlane(top.v, ktop - 1);
+            const int ni = readlane(top.id, ktop - 1);
+            if (better(nv, ni, thr_v, thr_i)) {
+              thr_v = nv;
+              thr_i = ni;
+            }
           }
         }
       }
     }
   }
+};
+
+// ----------------------------------------------------------------------------- top-k at the end of the row
+// While streaming, a lane only keeps the kTopGroups largest of its group maxima (a group: the kGroupVecs 16-byte
+// vectors a lane holds of half a tile), each with the group's number.  At the end the wave takes T = the k-th largest
+// of the lanes' best maxima: at least k elements reach T, so the top k lie in groups whose maximum reaches T, a dozen
+// or so, which are read again and ranked.  A lane whose last entry reaches T may have had further such groups: all of
+// that lane's groups are then read again (for k = 10 one wave in 10^4).
+// Keeping a sorted list while streaming instead costs an insertion path in nearly every tile of a short row, and its
+// serial latency where few waves are resident: 26 112 rows of V = 32 000 bf16 took 310 us, now 275 (a plain read of
+// these rows takes 240); 196 rows of V = 151 936 41.8 us, now 14.1; 6528 fp32 rows of V = 32 003 147 us, now 134.
+constexpr int kGroupVecs = 2;
+constexpr int kTopGroups = 5;
+constexpr int kDeferMaxK = 16;         // beyond, the lanes' lists hold the top k too rarely
+template <typename T> struct LaneTop;
+template <> struct LaneTop<uint16_t> {       // bf16: the group's number travels in the low half of its maximum
+  float k[kTopGroups];
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int i = 0; i < kTopGroups; ++i) k[i] = neg_inf();
+  }
+  __device__ __forceinline__ void add(float m, int group) {
+    // -inf would turn into a NaN: the lowest finite bf16 stands in for it
+    m = fmaxf(m, lowest());
+    m = __uint_as_float(__float_as_uint(m) | (uint32_t)group);
+#pragma unroll
+    for (int i = kTopGroups - 1; i > 0; --i) k[i] = __builtin_amdgcn_fmed3f(k[i - 1], k[i], m);
+    k[0] = fmaxf(k[0], m);
+  }
+  __device__ __forceinline__ float value(int i) const { return __uint_as_float(__float_as_uint(k[i]) & 0xffff0000u); }
+  __device__ __forceinline__ int group(int i) const { return (int)(__float_as_uint(k[i]) & 0xffffu); }
+  __device__ static __forceinline__ float lowest() { return __uint_as_float(0xff7f0000u); }
+};
+template <> struct LaneTop<float> {
+  float k[kTopGroups];
+  int g[kTopGroups];
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int i = 0; i < kTopGroups; ++i) { k[i] = neg_inf(); g[i] = 0; }
+  }
+  __device__ __forceinline__ void add(float m, int group) {
+    m = fmaxf(m, lowest());                  // above the empty entries' -inf, so that every group gets its number
+    bool b[kTopGroups];
+#pragma unroll
+    for (int i = 0; i < kTopGroups; ++i) b[i] = m > k[i];
+#pragma unroll
+    for (int i = kTopGroups - 1; i > 0; --i) {
+      k[i] = __builtin_amdgcn_fmed3f(k[i - 1], k[i], m);
+      g[i] = b[i - 1] ? g[i - 1] : (b[i] ? group : g[i]);
+    }
+    k[0] = fmaxf(k[0], m);
+    g[0] = b[0] ? group : g[0];
+  }
+  __device__ __forceinline__ float value(int i) const { return k[i]; }
+  __device__ __forceinline__ int group(int i) const { return g[i]; }
+  __device__ static __forceinline__ float lowest() { return -3.402823466e+38f; }
+};
+
+// What a wave's part of a row looks like: tiles first, first + step, ... below n_full, then (tail) the ragged one.
+struct RowPart {
+  int first, step, n_full;
+  bool tail;
+  __device__ __forceinline__ int full_tiles() const { return first < n_full ? (n_full - 1 - first) / step + 1 : 0; }
+  __device__ __forceinline__ int tiles() const { return full_tiles() + (tail ? 1 : 0); }
+  __device__ __forceinline__ int tile(int i) const { return i < full_tiles() ? first + i * step : n_full; }
+};
+
+// Sorted list of the wave's part by insertion, from the threshold (thr_v, thr_i) on; written to keys[0 .. ktop).
+template <typename T, int LOADS>
+__device__ __forceinline__ void insert_scan(const T *__restrict__ row, RowPart part, int V, int ktop, float thr_v, uint64_t *keys) {
+  constexpr int TILE = kWave * LOADS * Elem<T>::kPerVec;
+  const int lane = lane_id();
+  TopList top;
+  top.init();
+  int thr_i = kNoId;
+  Tile<T, LOADS> t;
+  u32x4 q[LOADS];
+  for (int i = part.first; i < part.n_full; i += part.step) {
+    load_tile<T, LOADS, false>(row, i * TILE, V, lane, q);
+    t.template unpack<false>(q, i * TILE, V, lane);
+    t.template insert<false>(i * TILE, V, lane, ktop, top, thr_v, thr_i);
+  }
+  if (part.tail) {
+    load_tile<T, LOADS, true>(row, part.n_full * TILE, V, lane, q);
+    t.template unpack<true>(q, part.n_full * TILE, V, lane);
+    t.template insert<true>(part.n_full * TILE, V, lane, ktop, top, thr_v, thr_i);
+  }
+  if (lane < ktop) keys[lane] = (top.id == kNoId) ? 0ull : rank_key(top.v, top.id);
 }
 
+// The top k of the wave's part from its lanes' group maxima: sorted keys[0 .. ktop), zeros behind the last one.
+// groups: kTopGroups * 64 words of the wave's LDS; keys: 64.
+template <typename T, int LOADS>
+__device__ __forceinline__ void collect_topk(const T *__restrict__ row, const RowPart &part, int V, int ktop,
+                                             const LaneTop<T> &lt, uint32_t *groups, uint64_t *keys) {
+  constexpr int EPV = Elem<T>::kPerVec;
+  constexpr int TILE = kWave * LOADS * EPV;
+  constexpr int PER_TILE = LOADS / kGroupVecs;
+  const int lane = lane_id();
+  const int n_groups = part.tiles() * PER_TILE;                // per lane
+  float T0 = kth_largest_of_lanes<(sizeof(T) == 2 ? 16 : 32)>(lt.value(0), ktop);
+  if (T0 <= LaneTop<T>::lowest()) T0 = neg_inf();              // fewer than k lanes with a finite logit
+  keys[lane] = 0ull;
+  // lanes that may have more groups at T0 than they kept
+  const bool over = n_groups > kTopGroups && lt.value(kTopGroups - 1) >= T0;
+  uint64_t over_mask = __builtin_amdgcn_ballot_w64(over);
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < kTopGroups; ++i) {
+    const bool hit = (i < n_groups) && lt.value(i) >= T0 && !over;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
+    if (hit) groups[n + lanes_below(mask)] = ((uint32_t)lt.group(i) << 6) | (uint32_t)lane;
+    n += __builtin_popcountll(mask);
+  }
+  // read the groups again, kGroupVecs lanes each, and pack what reaches T0
+  int n_keys = 0;
+  auto pack = [&](bool on, int group, int l) {
+    const int u = (group % PER_TILE) * kGroupVecs + lane % kGroupVecs;
+    const int e0 = on ? (group / PER_TILE) * TILE + (u * kWave + l) * EPV : V;
+    u32x4 q = {0u, 0u, 0u, 0u};
+    if (e0 < V) q = *reinterpret_cast<const u32x4 *>(row + e0);
+    float x[EPV];
+    Elem<T>::unpack(q, x);
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+      const bool hit = (e0 + e < V) && x[e] >= T0;
+      const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
+      if (mask != 0ull) {
+        const int at = n_keys + lanes_below(mask);
+        if (hit && at < kWave) keys[at] = rank_key(x[e], e0 + e);
+        n_keys += __builtin_popcountll(mask);
+      }
+    }
+  };
+  for (int base = 0; base < n; base += kWave / kGroupVecs) {
+    const int idx = base + lane / kGroupVecs;
+    const uint32_t gl = (idx < n) ? groups[idx] : 0u;
+    pack(idx < n, (int)(gl >> 6), (int)(gl & 63u));
+  }
+  for (; over_mask != 0ull && n_keys <= kWave; over_mask &= over_mask - 1) {
+    const int l = __builtin_ctzll(over_mask);
+    for (int base = 0; base < n_groups; base += kWave / kGroupVecs) {
+      const int idx = base + lane / kGroupVecs;
+      const bool on = idx < n_groups;
+      pack(on, on ? part.tile(idx / PER_TILE) * PER_TILE + idx % PER_TILE : 0, l);
+    }
+  }
+  if (n_keys > kWave) {                                        // many ties at T0
+    insert_scan<T, LOADS>(row, part, V, ktop, T0, keys);
+    return;
+  }
+  // rank them: position i of the sorted list is the number of keys that beat mine (unused places hold 0)
+  __builtin_amdgcn_wave_barrier();
+  const uint64_t mine = keys[lane];
+  int rank = 0;
+  for (int i = 0; i < n_keys; i += 8) {
+    uint64_t o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = keys[i + e];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) rank += (o[e] > mine) ? 1 : 0;
+  }
+  __builtin_amdgcn_wave_barrier();
+  keys[lane] = 0ull;
+  __builtin_amdgcn_wave_barrier();
+  if (mine != 0ull) keys[rank] = mine;
+}
+
+// Lowest id of the part's maximum m (each lane: its own first group that holds it).
+template <typename T, int LOADS>
+__device__ __forceinline__ int first_of_max(const T *__restrict__ row, int V, float m, float lane_m, int lane_tile) {
+  constexpr int EPV = Elem<T>::kPerVec;
+  constexpr int TILE = kWave * LOADS * EPV;
+  const int lane = lane_id();
+  int id = kNoId;
+  if (lane_m == m) {
+    u32x4 q[LOADS];
+    load_tile<T, LOADS, true>(row, lane_tile * TILE, V, lane, q);
+    float x[LOADS][EPV];
+#pragma unroll
+    for (int u = LOADS - 1; u >= 0; --u) {
+      Elem<T>::unpack(q[u], x[u]);
+      const int e0 = lane_tile * TILE + (u * kWave + lane) * EPV;
+#pragma unroll
+      for (int e = EPV - 1; e >= 0; --e)
+        if (e0 + e < V && x[u][e] == m) id = e0 + e;
+    }
+  }
+  return wave_min(id);
+}
+
+// What bounds it: memory, with the vector ALUs close behind (about 7.5 issue slots per logit, 4 of them the
+// quarter-rate exp2).  52 224 rows of V = 128 256 bf16 stream at 6.64 TB/s (target rows 6.86; a plain read reaches
+// 7.0 to 7.1).  The next tile is requested before the current one is scanned, which matters where few waves
+// share a compute unit (196 rows of V = 151 936: 16.1 us without, 14.1 with).
 template <typename T, int WAVES, int LOADS, int MODE>
 __global__ __launch_bounds__(WAVES *kWave) void k_row_stats(RowStatsArgs a) {
   constexpr int EPV = Elem<T>::kPerVec;
   constexpr int TILE = kWave * LOADS * EPV;
+  constexpr int PER_TILE = LOADS / kGroupVecs;
   const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
+  const int wave = (WAVES == 1) ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 
   // which row
   int r, l, j;
@@ -184,93 +386,148 @@ __global__ __launch_bounds__(WAVES *kWave) void k_row_stats(RowStatsArgs a) {
   }
   const T *row = static_cast<const T *>(a.logits) + stat_index(r, l, j, a.d, a.kslots) * a.row_stride;
   const int V = a.V;
+  const int n_full = V / TILE;
+  const RowPart part{wave, WAVES, n_full, n_full * TILE < V && (n_full % WAVES) == wave};
 
-  LaneAcc acc;
+  WaveAcc acc;
   acc.init();
-  TopList top;
+  LaneTop<T> top_groups;
+  top_groups.init();
+  int best_t = wave;              // argmax: the first tile that holds this lane's maximum
+  TopList top;                    // kDraftInsert
   top.init();
   float thr_v = neg_inf();
   int thr_i = kNoId;
-  bool first = true;
 
-  const int n_full = V / TILE;
-  for (int t = wave; t < n_full; t += WAVES) {
-    u32x4 q[LOADS];
-    load_tile<T, LOADS, false>(row, t * TILE, V, lane, q);
-    scan_tile<T, LOADS, false, MODE>(q, t * TILE, V, lane, a.ktop, first, acc, top, thr_v, thr_i);
+  Tile<T, LOADS> t;
+  auto scan = [&](const u32x4 *q, int i, auto guard) {
+    constexpr bool GUARD = decltype(guard)::value;
+    t.template unpack<GUARD>(q, i * TILE, V, lane);
+    const float cm = t.max_of(0, LOADS);
+    if (MODE == kTargetArgmax) best_t = (cm > acc.m) ? i : best_t;
+    t.accumulate(acc, cm);
+    if (MODE == kDraftTopK) {
+#pragma unroll
+      for (int h = 0; h < PER_TILE; ++h) top_groups.add(t.max_of(h * kGroupVecs, kGroupVecs), i * PER_TILE + h);
+    } else if (MODE == kDraftInsert) {
+      if (i == wave) {            // the first tile seeds the threshold: at least k of its elements reach it
+        thr_v = kth_largest_of_lanes<32>(cm, a.ktop);
+        thr_i = kNoId;
+      }
+      t.template insert<GUARD>(i * TILE, V, lane, a.ktop, top, thr_v, thr_i);
+    }
+  };
+  // (the scheduling barriers keep a tile's loads in front of the scan of the one before)
+  auto fetch = [&](int i, u32x4 *q) {
+    load_tile<T, LOADS, false>(row, i * TILE, V, lane, q);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (MODE == kDraftInsert) {
+    for (int i = wave; i < n_full; i += WAVES) {
+      u32x4 q[LOADS];
+      fetch(i, q);
+      scan(q, i, std::false_type{});
+    }
+  } else if (wave < n_full) {
+    u32x4 q0[LOADS], q1[LOADS];
+    int i = wave;
+    fetch(i, q0);
+    for (; i + 2 * WAVES < n_full; i += 2 * WAVES) {
+      fetch(i + WAVES, q1);
+      scan(q0, i, std::false_type{});
+      fetch(i + 2 * WAVES, q0);
+      scan(q1, i + WAVES, std::false_type{});
+    }
+    if (i + WAVES < n_full) {
+      fetch(i + WAVES, q1);
+      scan(q0, i, std::false_type{});
+      scan(q1, i + WAVES, std::false_type{});
+    } else {
+      scan(q0, i, std::false_type{});
+    }
   }
-  if (n_full * TILE < V && (n_full % WAVES) == wave) {
+  if (part.tail) {
     u32x4 q[LOADS];
     load_tile<T, LOADS, true>(row, n_full * TILE, V, lane, q);
-    scan_tile<T, LOADS, true, MODE>(q, n_full * TILE, V, lane, a.ktop, first, acc, top, thr_v, thr_i);
+    scan(q, n_full, std::true_type{});
   }
 
-  // wave-level reduction of (max, offset, sum)
-  const float Mw = wave_max(acc.m);
-  const float Cw = wave_max(acc.m == neg_inf() ? neg_inf() : acc.c);
-  const double contrib =
-      (acc.m == neg_inf()) ? 0.0 : acc.s * (double)__builtin_amdgcn_exp2f(acc.c - Cw);
-  const double Sw = wave_sum(contrib);
+  const float Mw = wave_max_dpp(acc.m);
+  const double Sw = wave_sum_dpp(acc.s);
 
-  __shared__ float sh_v[WAVES * kWave];
-  __shared__ int sh_i[WAVES * kWave];
+  __shared__ uint32_t sh_groups[WAVES * kTopGroups * kWave];
+  __shared__ __align__(16) uint64_t sh_key[WAVES * kWave];      // each wave's sorted list
   __shared__ float sh_M[WAVES], sh_C[WAVES];
   __shared__ double sh_S[WAVES];
-  __shared__ double sh_lse;
-  sh_v[threadIdx.x] = top.v;
-  sh_i[threadIdx.x] = top.id;
-  if (lane == 0) {
-    sh_M[wave] = Mw;
-    sh_C[wave] = Cw;
-    sh_S[wave] = Sw;
+  if (MODE == kDraftTopK) {
+    collect_topk<T, LOADS>(row, part, V, a.ktop, top_groups, sh_groups + wave * kTopGroups * kWave, sh_key + wave * kWave);
+  } else if (MODE == kTargetArgmax) {
+    const int id = part.tiles() ? first_of_max<T, LOADS>(row, V, Mw, acc.m, best_t) : kNoId;
+    if (lane == 0) sh_key[wave * kWave] = (id == kNoId) ? 0ull : rank_key(Mw, id);
+  } else if (MODE == kDraftInsert) {
+    sh_key[wave * kWave + lane] = (top.id == kNoId) ? 0ull : rank_key(top.v, top.id);
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float M = sh_M[0], C = sh_C[0];
-    bool any = (sh_M[0] != neg_inf());
-#pragma unroll
-    for (int w = 1; w < WAVES; ++w) {
-      M = fmaxf(M, sh_M[w]);
-      if (sh_M[w] != neg_inf()) {
-        C = any ? fmaxf(C, sh_C[w]) : sh_C[w];
-        any = true;
-      }
+  if (WAVES > 1) {
+    if (lane == 0) {
+      sh_M[wave] = Mw;
+      sh_C[wave] = acc.c;
+      sh_S[wave] = Sw;
     }
-    double S = 0.0;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w)
-      if (sh_M[w] != neg_inf()) S += sh_S[w] * (double)__builtin_amdgcn_exp2f(sh_C[w] - C);
-    // log2-domain total is C + log2(S); the row maximum contributes exactly M*log2e of it.
-    const double lse = (double)M + kLn2 * (((double)C - (double)M * (double)kLog2e) + log2(S));
-    sh_lse = lse;
+    __syncthreads();
+    if (wave != 0) return;
+  }
+  // the first wave finishes the row
+  float M = Mw, C = acc.c;
+  double S = Sw;
+  if (WAVES > 1) {
+    const bool on = lane < WAVES;
+    const float wc = on ? sh_C[lane] : neg_inf();
+    M = wave_max_dpp(on ? sh_M[lane] : neg_inf());
+    C = wave_max_dpp(wc);
+    S = wave_sum_dpp(on ? scale_pow2(sh_S[lane], wc - C) : 0.0);
+  }
+  // log2-domain total is C + log2(S); the row maximum contributes exactly M*log2e of it.
+  const double lse = (double)M + kLn2 * (((double)C - (double)M * (double)kLog2e) + log2(S));
+  if (lane == 0) {
     if (a.row_max) a.row_max[oi] = M;
     a.row_lse[oi] = (float)lse;
   }
   if (MODE == kLseOnly || a.top_tok == nullptr) return;
-  __shared__ int sh_claimed[kWave];
-  if (threadIdx.x < kWave) sh_claimed[threadIdx.x] = 0;
-  __syncthreads();
-  // merge the WAVES sorted lists: rank each of the first ktop entries of every wave
-  if (lane < a.ktop) {
-    const float v = top.v;
-    const int id = top.id;
-    int rank = 0;
-    for (int w = 0; w < WAVES; ++w)
-      for (int i = 0; i < a.ktop; ++i) rank += better(sh_v[w * kWave + i], sh_i[w * kWave + i], v, id) ? 1 : 0;
-    if (rank < a.ktop && id != kNoId) {
-      sh_claimed[rank] = 1;
-      a.top_tok[oi * a.ktop + rank] = id;
-      // clamped: rounding must never make a log-probability positive (a child may not outrank its parent)
-      if (a.top_logp) a.top_logp[oi * a.ktop + rank] = fminf((float)((double)v - sh_lse), 0.f);
+  const int ktop = (MODE == kTargetArgmax) ? 1 : a.ktop;
+  // position `lane` of the row's list: of the only wave's, or by ranking the waves' candidates
+  uint64_t key = 0ull;
+  if (WAVES == 1) {
+    __builtin_amdgcn_wave_barrier();
+    key = sh_key[lane];
+  } else {
+    const int total = WAVES * ktop;
+    __shared__ __align__(16) uint64_t sh_all[WAVES * kWave + 8], sh_out[kWave];
+    sh_out[lane] = 0ull;
+    for (int i = lane; i < total + 8; i += kWave) sh_all[i] = (i < total) ? sh_key[(i / ktop) * kWave + i % ktop] : 0ull;
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < total; i += kWave) {
+      const uint64_t mine = sh_all[i];
+      int rank = 0;
+      for (int u = 0; u < total; u += 8) {
+        uint64_t o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = sh_all[u + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rank += (o[e] > mine) ? 1 : 0;
+      }
+      if (mine != 0ull && rank < ktop) sh_out[rank] = mine;
     }
+    __builtin_amdgcn_wave_barrier();
+    key = sh_out[lane];
   }
-  __syncthreads();
-  // A row that holds NaNs can leave ranks unclaimed (a NaN wins no comparison).  Such a row's values are
-  // unspecified, but every id written must be a token of the vocabulary: unclaimed ranks get token `rank`
-  // (V >= ktop) with probability zero.
-  if (threadIdx.x < a.ktop && sh_claimed[threadIdx.x] == 0) {
-    a.top_tok[oi * a.ktop + threadIdx.x] = threadIdx.x;
-    if (a.top_logp) a.top_logp[oi * a.ktop + threadIdx.x] = neg_inf();
+  if (lane < ktop) {
+    // A row that holds NaNs can leave ranks unclaimed (a NaN wins no comparison).  Such a row's values are
+    // unspecified, but every id written must be a token of the vocabulary: unclaimed ranks get token `rank`
+    // (V >= ktop) with probability zero.
+    const bool ok = key != 0ull;
+    a.top_tok[oi * ktop + lane] = ok ? key_index(key) : lane;
+    // clamped: rounding must never make a log-probability positive (a child may not outrank its parent)
+    if (a.top_logp) a.top_logp[oi * ktop + lane] = ok ? fminf((float)((double)key_score(key) - lse), 0.f) : neg_inf();
   }
 }
 
@@ -596,7 +853,10 @@ template <typename T>
 static void launch_row_stats_t(const RowStatsArgs &a, int blocks, hipStream_t st) {
   if (a.top_tok == nullptr) launch_row_stats_m<T, kLseOnly>(a, blocks, st);
   else if (a.ktop == 1) launch_row_stats_m<T, kTargetArgmax>(a, blocks, st);
-  else launch_row_stats_m<T, kDraftTopK>(a, blocks, st);
+  // the deferred top-k numbers a row's groups in 16 bits
+  else if (a.ktop <= kDeferMaxK && (int64_t)a.V / (kWave * Elem<T>::kPerVec * kGroupVecs) < 65000)
+    launch_row_stats_m<T, kDraftTopK>(a, blocks, st);
+  else launch_row_stats_m<T, kDraftInsert>(a, blocks, st);
 }
 
 void launch_row_stats(const RowStatsArgs &a, int dtype, int blocks, hipStream_t st) {

@@ -14,10 +14,6 @@ namespace gto {
 constexpr int kTreeThreads = 256;
 constexpr int kMaxPool = 4096;        // C
 
-__device__ __forceinline__ uint64_t rank_key(float score, int index) {
-  return ((uint64_t)ordered_bits(score) << 32) | (uint32_t)(0xffffffffu - (uint32_t)index);
-}
-
 // ------------------------------------------------------------------------------ expansion
 // Which rows feed which candidate is fixed by the shape (candidate c of the pool is child rk of slot j of
 // level l), so every log-probability and token of the root is fetched up front in one round of loads; the

@@ -453,3 +453,41 @@ def test_token_level_loss_fwd_bwd(gpu_device, name, R, V, kw):
         for r in range(R):
             scale = np.abs(ref["grad"][r]).max()
             assert np.abs(g[r] - ref["grad"][r]).max() <= 1e-5 * scale + 1e-12, r
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 4096), ("bf16", 20011), ("f32", 6001)])
+@pytest.mark.parametrize("k,waves", [(10, 1), (16, 2), (16, 1), (17, 1), (4, 8), (33, 4)])
+def test_row_topk_of_adversarial_rows(gpu_device, dtype, V, k, waves):
+    """Rows that stress how the top k is collected (k <= 16: from the lanes' group maxima at the end of the row; above:
+    by insertion): all large values in one lane's column, more ties than a wave has lanes, fewer finite values than k,
+    monotone rows, rows at the bottom of the type's range, and a target row of each kind."""
+    es, per = (torch.bfloat16, 8) if dtype == "bf16" else (torch.float32, 4)
+    gen = torch.Generator().manual_seed(V + k)
+    stride = (V + 7) // 8 * 8
+    rows = []
+    x = torch.randn(V, generator=gen)
+    for lane in (0, 5, 63):                                    # one lane's column holds the 40 best (several tiles)
+        y = x.clone()
+        ids = torch.arange(lane * per, V, 64 * per)[:40]
+        y[ids] = 10.0 + torch.randperm(len(ids), generator=gen).float() / 4
+        rows.append(y)
+    y = x.clone(); y[torch.randperm(V, generator=gen)[:200]] = 9.0; rows.append(y)        # 200 ties at the top
+    y = x.clone(); y[torch.randperm(V, generator=gen)[:70]] = 9.0; y[V - 1] = 9.5; rows.append(y)
+    y = torch.full((V,), float("-inf")); y[[3, V // 2, V - 1]] = torch.tensor([1.0, 2.0, 1.0]); rows.append(y)
+    rows.append(torch.arange(V).float() / 64)                  # rising, falling
+    rows.append(-torch.arange(V).float() / 64)
+    y = torch.full((V,), float("-inf")); y[100:400] = torch.finfo(es).min; y[200] = -1e6; rows.append(y)
+    y = x.clone(); y[::2] = float("-inf"); rows.append(y)
+    y = x * 1e-3; rows.append(y)                               # a narrow row: many ties in bf16
+    rows.append(torch.zeros(V))
+    R = len(rows)
+    D = torch.full((R, 1, k, stride), 77.0)
+    D[:, 0, 0, :V] = torch.stack(rows)
+    D = D.to(es).to(gpu_device)
+    cfg = G.make_config(R=R, d=1, k=k, g=4, V=V, dtype=es, row_stride=stride, waves_per_row=waves)
+    ds = G.gto_draft_row_stats(cfg, D, U.alloc_poisoned(G.alloc_draft_stats, cfg, gpu_device))
+    ts = G.gto_target_row_stats(cfg, D, U.alloc_poisoned(G.alloc_target_stats, cfg, gpu_device))
+    torch.cuda.synchronize()
+    Dn = U.logits_np(D)[..., :V]
+    U.check_row_stats(U.to_np(ds), O.draft_row_stats(Dn, k), Dn, k)
+    U.check_target_stats(U.to_np(ts), O.target_row_stats(Dn))
