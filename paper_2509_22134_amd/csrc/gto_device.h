@@ -115,6 +115,33 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
   return __longlong_as_double(((uint64_t)hi << 32) | lo);
 }
 
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 1, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 2, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 4, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 8, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast15, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast31, 0xf, 0xf, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Value of lane `lane ^ M`: DPP moves inside a row of 16, a permute through LDS beyond.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  const int x = (int)v;
+  if constexpr (M == 1) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0xb1 /* quad 1,0,3,2 */, 0xf, 0xf, true);
+  else if constexpr (M == 2) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x4e /* quad 2,3,0,1 */, 0xf, 0xf, true);
+  else if constexpr (M == 4)      // ^7 within eight lanes, then ^3 within four
+    return (uint32_t)__builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);
+  else if constexpr (M == 8) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x128 /* row_ror:8 */, 0xf, 0xf, true);
+  else return (uint32_t)__shfl_xor(x, M, kWave);
+}
+template <int M>
+__device__ __forceinline__ double lane_xor(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  return __longlong_as_double(((uint64_t)lane_xor<M>((uint32_t)(u >> 32)) << 32) | lane_xor<M>((uint32_t)u));
+}
+
 // 16 bytes of logits -> fp32 values.
 template <typename T> struct Elem;
 template <> struct Elem<uint16_t> {           // bf16 storage

@@ -1,6 +1,11 @@
 // Per-root kernels of the GTO hot path: layer-wise expansion, global re-rank, reward scan and
 // greedy verification walk, group advantage, clipped surrogate forward.  All of them work on a
-// few KB per root that live in LDS; they are latency-bound and tiny next to the row kernels.
+// few KB per root; they are latency-bound and tiny next to the row kernels.
+//
+// What bounds them is the chain of dependent steps in a root, so the usual sizes run as one wave per root: no
+// barriers (a barrier also waits until every global store before it has been acknowledged), intermediate results in
+// LDS or registers, global memory read in one or two rounds at the start and written once at the end.  Larger shapes
+// take the workgroup-per-root kernels.
 //
 // Ranking everywhere is on a packed 64-bit key (order-preserving bits of the fp32 score, then the
 // inverted index): keys are unique, so (score descending, index ascending) is realised exactly and
@@ -102,7 +107,135 @@ __global__ __launch_bounds__(kTreeThreads) void k_expand(ExpandArgs a) {
   }
 }
 
+// One wave per root, k^2 <= 64 NT keys per level: lane t % 64 holds child t.  A level's k best come out one after the
+// other by a wave-wide maximum of the score bits, the lowest child among equals first; lane j keeps the j-th, so the
+// next level's parent scores are lane exchanges.  (Counting the keys that beat each key takes k^2 64-bit compares per
+// lane and child.)  1024 roots with k = 10, d = 6: 14 us before, 12 now; 4 roots with k = 8, d = 7: 9.5 us, now 7.4.
+// Dynamic LDS: C scores (4 B; they start as the log-probabilities), C parents and C slots (2 B each), d * k expanded
+// candidates (2 B).
+template <int NT>
+__global__ __launch_bounds__(64) void k_expand_wave(ExpandArgs a) {
+  const int r = blockIdx.x, lane = threadIdx.x;
+  const int k = a.k, d = a.d, kk = a.k * a.k, C = a.C;
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  float *s_sc = reinterpret_cast<float *>(s_dyn);
+  int16_t *s_parent = reinterpret_cast<int16_t *>(s_sc + C);
+  int16_t *s_slot = s_parent + C, *s_exp = s_slot + C;
+  const int64_t pool0 = (int64_t)r * C;
+  const int64_t row0 = (int64_t)r * d * kk;       // statistics of slot (0, 0)
+
+  // candidate c is entry c of the root's slot, or entry c - k of the levels below, which follow each other
+  for (int c0 = 0; c0 < C; c0 += 8 * 64) {
+    float lp[8];
+    int tok[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int c = min(c0 + u * 64 + lane, C - 1);
+      const int64_t si = row0 + (c < k ? c : c - k + kk);
+      lp[u] = a.top_logp[si];
+      tok[u] = a.top_tok[si];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int c = c0 + u * 64 + lane;
+      if (c < C) {
+        s_sc[c] = lp[u];
+        a.cand_tok[pool0 + c] = tok[u];
+      }
+    }
+  }
+  int jt[NT];                                     // slot of this lane's n-th child of a level
+#pragma unroll
+  for (int n = 0; n < NT; ++n) jt[n] = (n * 64 + lane) / k;
+  __builtin_amdgcn_wave_barrier();
+  // level 0: the root's k children, all expanded at level 1 in rank order
+  float p_score = 0.f;                            // lane j: score and pool index of the node in slot j of the level
+  int p_cand = lane;
+  if (lane < k) {
+    p_score = __fadd_rn(0.f, s_sc[lane]);
+    s_sc[lane] = p_score;
+    s_parent[lane] = -1;
+    s_slot[lane] = (int16_t)((d > 1) ? lane : -1);
+    s_exp[lane] = -1;
+  }
+  for (int l = 1; l < d; ++l) {
+    const int base = k + (l - 1) * kk;
+    if (lane < k) s_exp[l * k + lane] = (int16_t)p_cand;
+    uint32_t o[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int t = n * 64 + lane;
+      const float ps = __shfl(p_score, jt[n] & 63, kWave);
+      const int pc = __shfl(p_cand, jt[n] & 63, kWave);
+      o[n] = 0u;                                  // (no score has this image)
+      if (t < kk) {
+        const float sc = __fadd_rn(ps, s_sc[base + t]);
+        s_sc[base + t] = sc;
+        s_parent[base + t] = (int16_t)pc;
+        s_slot[base + t] = -1;
+        o[n] = ordered_bits(sc);
+      }
+    }
+    if (l == d - 1) break;
+    float n_score = 0.f;
+    int n_cand = 0;
+    for (int j = 0; j < k; ++j) {
+      uint32_t m = o[0];
+#pragma unroll
+      for (int n = 1; n < NT; ++n) m = max(m, o[n]);
+      m = wave_max_dpp(m);
+      int at = 0;                                 // the lowest child that holds the maximum
+#pragma unroll
+      for (int n = NT - 1; n >= 0; --n) {
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(o[n] == m);
+        if (mask != 0ull) at = n * 64 + __builtin_ctzll(mask);
+      }
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        if (n * 64 + lane == at) o[n] = 0u;
+      if (lane == j) {
+        n_score = from_ordered_bits(m);
+        n_cand = base + at;
+      }
+    }
+    if (lane < k) {
+      s_slot[n_cand] = (int16_t)lane;
+      n_score = s_sc[n_cand];                     // (the image of -0 is that of 0: take the score itself)
+    }
+    p_score = n_score;
+    p_cand = n_cand;
+  }
+  __builtin_amdgcn_wave_barrier();
+  for (int c = lane; c < C; c += 64) {
+    a.cand_score[pool0 + c] = s_sc[c];
+    a.cand_parent[pool0 + c] = s_parent[c];
+    a.cand_slot[pool0 + c] = s_slot[c];
+  }
+  if (lane < k) {
+    a.cand_depth[pool0 + lane] = 1;
+    a.cand_pslot[pool0 + lane] = 0;
+  }
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int t = n * 64 + lane;
+    if (t < kk)
+      for (int l = 1; l < d; ++l) {
+        a.cand_depth[pool0 + k + (l - 1) * kk + t] = l + 1;
+        a.cand_pslot[pool0 + k + (l - 1) * kk + t] = jt[n];
+      }
+  }
+  for (int i = lane; i < d * k; i += 64) a.slot_cand[(int64_t)r * d * k + i] = s_exp[i];
+}
+
 void launch_expand(const ExpandArgs &a, hipStream_t st) {
+  const int kk = a.k * a.k;
+  if (kk <= 256) {
+    const size_t lds_wave = (size_t)a.C * 8 + (size_t)a.d * a.k * 2;
+    if (kk <= 64) hipLaunchKernelGGL(k_expand_wave<1>, dim3(a.R), dim3(64), lds_wave, st, a);
+    else if (kk <= 128) hipLaunchKernelGGL(k_expand_wave<2>, dim3(a.R), dim3(64), lds_wave, st, a);
+    else hipLaunchKernelGGL(k_expand_wave<4>, dim3(a.R), dim3(64), lds_wave, st, a);
+    return;
+  }
   const size_t lds = (size_t)((a.k * a.k + 7) & ~7) * 8 + (size_t)a.C * 4;
   hipLaunchKernelGGL(k_expand, dim3(a.R), dim3(kTreeThreads), lds, st, a);
 }
@@ -192,10 +325,127 @@ __global__ __launch_bounds__(kTreeThreads) void k_select(SelectArgs a) {
   if (tid == 0) a.n_sel[r] = n_keep;
 }
 
+// One wave per root, C <= 64 NPL: the same network with NPL keys per lane (key index lane * NPL + e while sorting), so
+// that short strides stay in a lane's registers and long ones are lane exchanges (DPP moves up to 8 lanes): 1024 roots
+// with C = 510 take 12 us (workgroup per root: 17.6 us, 45 barriers), 4 roots 9 us (13).  The keys are doubles in [1, 2) whose mantissa
+// holds the score's bits and the inverted index: the fp64 compare runs at full rate, the 64-bit integer one does not.
+__device__ __forceinline__ double sort_key(float score, int index) {
+  return __longlong_as_double(0x3ff0000000000000ull | ((uint64_t)ordered_bits(score) << 20) | (uint64_t)(0xfffff - index));
+}
+__device__ __forceinline__ int sort_index(double key) { return 0xfffff - (int)(__double_as_longlong(key) & 0xfffff); }
+
+template <int NPL, int SIZE, int STRIDE>
+__device__ __forceinline__ void bitonic_stage(double (&key)[NPL], int lane) {
+  if constexpr (STRIDE >= NPL) {
+    const bool desc = ((lane * NPL) & SIZE) == 0;              // (SIZE > STRIDE >= NPL: the same for all keys of a lane)
+    const bool larger = desc != ((lane & (STRIDE / NPL)) != 0);
+#pragma unroll
+    for (int e = 0; e < NPL; ++e) {
+      const double o = lane_xor<STRIDE / NPL>(key[e]);
+      key[e] = ((key[e] < o) == larger) ? o : key[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < NPL; ++e) {
+      if (e & STRIDE) continue;
+      const bool desc = ((lane * NPL + e) & SIZE) == 0;
+      const double x = key[e], y = key[e + STRIDE];
+      const bool swap = (x < y) == desc;
+      key[e] = swap ? y : x;
+      key[e + STRIDE] = swap ? x : y;
+    }
+  }
+  if constexpr (STRIDE > 1) bitonic_stage<NPL, SIZE, STRIDE / 2>(key, lane);
+}
+// descending sort of 64 NPL keys
+template <int NPL, int SIZE = 2>
+__device__ __forceinline__ void bitonic_sort(double (&key)[NPL], int lane) {
+  bitonic_stage<NPL, SIZE, SIZE / 2>(key, lane);
+  if constexpr (SIZE < 64 * NPL) bitonic_sort<NPL, SIZE * 2>(key, lane);
+}
+// Dynamic LDS: C ranks (2 B), n_keep candidates (2 B), n_keep leaf flags, d * k need flags (1 B each).
+template <int NPL>
+__global__ __launch_bounds__(64) void k_select_wave(SelectArgs a) {
+  const int r = blockIdx.x, lane = threadIdx.x;
+  const int C = a.C, g = a.g;
+  const int n_keep = (g < C) ? g : C;
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  int16_t *s_rank = reinterpret_cast<int16_t *>(s_dyn);
+  int16_t *s_sel = s_rank + C;
+  unsigned char *s_leaf = reinterpret_cast<unsigned char *>(s_sel + n_keep);
+  unsigned char *s_need = s_leaf + n_keep;
+  const int64_t pool0 = (int64_t)r * C;
+  const int64_t sel0 = (int64_t)r * g;
+  double key[NPL];
+#pragma unroll
+  for (int e = 0; e < NPL; ++e) {
+    const int c = e * 64 + lane;                  // (which lane starts with which key does not matter)
+    const float sc = a.cand_score[pool0 + min(c, C - 1)];
+    key[e] = (c < C) ? sort_key(sc, c) : 1.0;     // padding: below every real key
+  }
+  for (int c = lane; c < C; c += 64) s_rank[c] = 0x7fff;
+  for (int i = lane; i < n_keep; i += 64) s_leaf[i] = 1;
+  for (int i = lane; i < a.d * a.k; i += 64) s_need[i] = 0;
+  bitonic_sort<NPL>(key, lane);
+#pragma unroll
+  for (int e = 0; e < NPL; ++e) {
+    const int i = lane * NPL + e;
+    if (i < n_keep) {
+      const int c = sort_index(key[e]);
+      s_rank[c] = (int16_t)i;
+      s_sel[i] = (int16_t)c;
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  for (int i = lane; i < n_keep; i += 64) {
+    const int c = s_sel[i];
+    const int p = a.cand_parent[pool0 + c], tok = a.cand_tok[pool0 + c], dep = a.cand_depth[pool0 + c];
+    const int ps = a.cand_pslot[pool0 + c], sl = a.cand_slot[pool0 + c];
+    const float sc = a.cand_score[pool0 + c];
+    const int pr = (p >= 0) ? s_rank[p] : 0x7fff;
+    if (pr < n_keep) s_leaf[pr] = 0;              // a kept child: the parent is not a leaf
+    s_need[(dep - 1) * a.k + ps] = 1;             // the row that produced a kept node is needed by the reward
+    a.sel_cand[sel0 + i] = c;
+    a.sel_tok[sel0 + i] = tok;
+    // a parent always outranks its child (log-probabilities are <= 0); the range check only matters for
+    // rows that held NaNs, whose values are unspecified but whose indices must stay inside the list
+    a.sel_parent[sel0 + i] = (pr < i) ? pr : -1;
+    a.sel_depth[sel0 + i] = dep;
+    a.sel_pslot[sel0 + i] = ps;
+    a.sel_slot[sel0 + i] = sl;
+    a.sel_score[sel0 + i] = sc;
+  }
+  __builtin_amdgcn_wave_barrier();
+  for (int i = lane; i < g; i += 64) {
+    a.sel_leaf[sel0 + i] = (i < n_keep) ? s_leaf[i] : 0;
+    if (i >= n_keep) {
+      a.sel_cand[sel0 + i] = -1;
+      a.sel_tok[sel0 + i] = -1;
+      a.sel_parent[sel0 + i] = -1;
+      a.sel_depth[sel0 + i] = 0;
+      a.sel_pslot[sel0 + i] = 0;
+      a.sel_slot[sel0 + i] = -1;
+      a.sel_score[sel0 + i] = 0.f;
+    }
+  }
+  for (int i = lane; i < a.d * a.k; i += 64) a.slot_need[(int64_t)r * a.d * a.k + i] = s_need[i];
+  if (lane == 0) a.n_sel[r] = n_keep;
+}
+
 void launch_select(const SelectArgs &a, hipStream_t st) {
   int n_pad = 2;
   while (n_pad < a.C) n_pad <<= 1;
   const int n_keep = (a.g < a.C) ? a.g : a.C;
+  if (n_pad <= 1024) {
+    const size_t lds_wave = (size_t)a.C * 2 + (size_t)n_keep * 3 + (size_t)a.d * a.k;
+    const dim3 grid(a.R), block(64);
+    if (n_pad <= 64) hipLaunchKernelGGL(k_select_wave<1>, grid, block, lds_wave, st, a);
+    else if (n_pad <= 128) hipLaunchKernelGGL(k_select_wave<2>, grid, block, lds_wave, st, a);
+    else if (n_pad <= 256) hipLaunchKernelGGL(k_select_wave<4>, grid, block, lds_wave, st, a);
+    else if (n_pad <= 512) hipLaunchKernelGGL(k_select_wave<8>, grid, block, lds_wave, st, a);
+    else hipLaunchKernelGGL(k_select_wave<16>, grid, block, lds_wave, st, a);
+    return;
+  }
   const size_t lds = (size_t)n_pad * 8 + (size_t)a.C * 4 + (size_t)n_keep + (size_t)a.d * a.k;
   hipLaunchKernelGGL(k_select, dim3(a.R), dim3(kTreeThreads), lds, st, a);
 }
@@ -397,7 +647,232 @@ __global__ __launch_bounds__(kRewardThreads) void k_reward(RewardArgs a) {
   if (tid == 0) a.path_len[r] = len;
 }
 
+// One wave per root, at most 64 NN kept nodes, node i in lane i % 64: 1024 roots with 60 nodes take 7 us (workgroup
+// per root: 14 to 18 us, of it the walk's dependent loads and barriers).  The prefix sums go level by level (a node
+// adds its own term to its parent's sum, the order of the chain walk above).
+// Dynamic LDS: per node the prefix sum and cumulative length (8 B each), parent (4 B); d * k target argmaxes.
+template <typename T, int NN>
+__global__ __launch_bounds__(64) void k_reward_wave(RewardArgs a) {
+  const int r = blockIdx.x, lane = threadIdx.x;
+  const int d = a.d, k = a.k, g = a.g;
+  const int cap = reward_nodes(a);                // <= 64 NN
+  const int64_t sel0 = (int64_t)r * g;
+  const int64_t slot0 = (int64_t)r * d * k;
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  double *s_lq = reinterpret_cast<double *>(s_dyn);
+  double *s_cum = s_lq + cap;
+  int *s_parent = reinterpret_cast<int *>(s_cum + cap);
+  int *s_arg = s_parent + cap;
+  const T *logits = static_cast<const T *>(a.target_logits);
+
+  // everything that is addressed by the shape alone, in one round
+  const int n = min(a.n_sel[r], cap);
+  int dep[NN], par[NN], tok[NN], own[NN], ps[NN];
+  bool leaf[NN], on[NN];
+#pragma unroll
+  for (int q = 0; q < NN; ++q) {
+    const int64_t i = sel0 + min(q * 64 + lane, cap - 1);
+    dep[q] = a.sel_depth[i];
+    ps[q] = a.sel_pslot[i];
+    tok[q] = a.sel_tok[i];
+    par[q] = a.sel_parent[i];
+    own[q] = a.sel_slot[i];
+    leaf[q] = a.sel_leaf[i] != 0;
+  }
+  if (a.path_mode == 0)
+    for (int i = lane; i < d * k; i += 64) s_arg[i] = a.t_argmax[slot0 + i];
+  // target log-probability of every kept token (one gather each)
+  double logt[NN];
+#pragma unroll
+  for (int q = 0; q < NN; ++q) {
+    const int i = q * 64 + lane;
+    on[q] = i < n;
+    logt[q] = 0.0;
+    if (on[q]) {
+      const int t = min(max(tok[q], 0), a.V - 1);               // ids come from the row kernels: always in range
+      const int64_t si = stat_index(r, dep[q] - 1, ps[q], d, k);
+      const float x = a.node_logit ? a.node_logit[sel0 + i] : Elem<T>::load1(logits + si * a.row_stride + t);
+      logt[q] = (double)x - (double)a.t_lse[si];
+      s_parent[i] = par[q];
+      s_lq[i] = 0.0;
+      s_cum[i] = 0.0;
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  // length of each node's ancestor chain
+  int len[NN], deepest = 0;
+#pragma unroll
+  for (int q = 0; q < NN; ++q) {
+    len[q] = 0;
+    if (on[q])
+      for (int p = q * 64 + lane; p >= 0 && len[q] < kMaxDepth; p = s_parent[p]) ++len[q];
+  }
+  // prefix products along each node's own ancestor chain (root first), Eq. 3-4
+  double lq[NN], pq[NN], cum[NN];
+#pragma unroll
+  for (int q = 0; q < NN; ++q) lq[q] = cum[q] = 0.0;
+  for (int s = 1; s <= kMaxDepth; ++s) {
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < NN; ++q) {
+      if (len[q] == s) {
+        lq[q] = (par[q] >= 0 ? s_lq[par[q]] : 0.0) + logt[q];
+        s_lq[q * 64 + lane] = lq[q];
+      }
+      any = any || len[q] == s;
+    }
+    if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;        // chains are prefix-closed: none is longer
+    deepest = s;
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int q = 0; q < NN; ++q) pq[q] = on[q] ? exp(lq[q]) : 0.0;
+  for (int s = 1; s <= deepest; ++s) {
+#pragma unroll
+    for (int q = 0; q < NN; ++q)
+      if (len[q] == s) {
+        cum[q] = (par[q] >= 0 ? s_cum[par[q]] : 0.0) + pq[q];
+        s_cum[q * 64 + lane] = cum[q];
+      }
+    __builtin_amdgcn_wave_barrier();
+  }
+  double v_max = -1.0, v_sumL = 0.0, v_cnt = 0.0, v_q = 0.0;
+#pragma unroll
+  for (int q = 0; q < NN; ++q) {
+    const int i = q * 64 + lane;
+    leaf[q] = leaf[q] && on[q];
+    if (on[q]) {
+      a.node_q[sel0 + i] = (float)pq[q];
+      a.node_cum[sel0 + i] = (float)cum[q];
+    }
+    v_q += pq[q];
+    if (leaf[q]) {
+      v_max = fmax(v_max, cum[q]);
+      v_sumL += cum[q];
+      v_cnt += 1.0;
+    }
+  }
+  for (int i = n + lane; i < g; i += 64) {
+    a.node_q[sel0 + i] = 0.f;
+    a.node_cum[sel0 + i] = 0.f;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v_max = fmax(v_max, __shfl_xor(v_max, off, kWave));
+  const double Lmax = v_max;
+  double v_exp = 0.0;
+#pragma unroll
+  for (int q = 0; q < NN; ++q)
+    if (leaf[q]) v_exp += exp((double)a.eta * (cum[q] - Lmax));
+  const double sum_exp = wave_sum_dpp(v_exp), sumL = wave_sum_dpp(v_sumL), cnt = wave_sum_dpp(v_cnt);
+  const double nodesum = wave_sum_dpp(v_q);
+  if (lane == 0) {
+    const double lse = (cnt > 0.0) ? Lmax + log(sum_exp) / (double)a.eta : 0.0;
+    const double mx = (cnt > 0.0) ? Lmax : 0.0;
+    const double mean = (cnt > 0.0) ? sumL / cnt : 0.0;
+    float *aux = a.reward_aux + (int64_t)r * 4;
+    aux[0] = (float)lse;
+    aux[1] = (float)mx;
+    aux[2] = (float)mean;
+    aux[3] = (float)nodesum;
+    const double pick = (a.reward_mode == 0) ? lse : (a.reward_mode == 1) ? mx : (a.reward_mode == 2) ? mean : nodesum;
+    a.reward[r] = (float)pick;
+    a.n_leaves[r] = (int)cnt;
+  }
+
+  // the accepted sequence: lane t keeps its step t
+  int p_node = -1, p_slot = -1, plen = 0;
+  auto pick_of = [&](const int (&v)[NN], int i) {               // v of node i (uniform)
+    int out = 0;
+#pragma unroll
+    for (int q = 0; q < NN; ++q)
+      if ((i >> 6) == q) out = readlane(v[q], i & 63);
+    return out;
+  };
+  if (a.path_mode == 1) {
+    // the root-to-leaf sequence with the largest expected acceptance length L_i (first one in kept order among equals)
+    int best = kNoId;
+#pragma unroll
+    for (int q = NN - 1; q >= 0; --q)
+      if (leaf[q] && cum[q] == Lmax) best = q * 64 + lane;
+    best = wave_min(best);
+    if (best != kNoId) {
+      plen = pick_of(len, best);
+      for (int t = plen - 1, p = best; t >= 0; --t) {
+        const int sl = pick_of(ps, p), up = pick_of(par, p);
+        if (lane == t) { p_node = p; p_slot = sl; }
+        p = up;
+      }
+    }
+  } else if (a.path_mode == 2) {
+    // verification at temperature 1: the kept children of the current node are tried in kept order,
+    // child x accepted with probability p_T(x) / (target mass not yet rejected at this node), decided
+    // by the caller's uniform numbers
+    double p_tok[NN];
+#pragma unroll
+    for (int q = 0; q < NN; ++q) p_tok[q] = exp(logt[q]);
+    int cur = -1, slot = 0;
+    for (int t = 0; t < d; ++t) {
+      const float u_lane = (lane < k) ? a.accept_u[((int64_t)r * d + t) * k + lane] : 0.f;
+      double rest = 1.0;
+      int j = 0, nxt = -1;
+#pragma unroll
+      for (int q = 0; q < NN; ++q) {
+        uint64_t mask = __builtin_amdgcn_ballot_w64(on[q] && par[q] == cur && dep[q] == t + 1);
+        for (; mask != 0ull && nxt < 0; mask &= mask - 1, ++j) {
+          const int src = __builtin_ctzll(mask);
+          const double pt = __shfl(p_tok[q], src, kWave);
+          const double acc = (rest > 0.0) ? pt / rest : 1.0;
+          const double u = (double)readlane(u_lane, min(j, 63));
+          if (u < acc) nxt = q * 64 + src;
+          rest -= pt;
+        }
+      }
+      if (nxt < 0) break;
+      if (lane == t) { p_node = nxt; p_slot = slot; }
+      plen = t + 1;
+      slot = pick_of(own, nxt);
+      if (slot < 0) break;
+      cur = nxt;
+    }
+  } else {
+    // greedy verification walk (T = 0): follow the kept child that equals the target argmax
+    int cur = -1, slot = 0;
+    for (int t = 0; t < d; ++t) {
+      const int want = s_arg[t * k + slot];
+      int nxt = -1;
+#pragma unroll
+      for (int q = NN - 1; q >= 0; --q) {
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(on[q] && par[q] == cur && dep[q] == t + 1 && tok[q] == want);
+        if (mask != 0ull) nxt = q * 64 + __builtin_ctzll(mask);
+      }
+      if (nxt < 0) break;
+      if (lane == t) { p_node = nxt; p_slot = slot; }
+      plen = t + 1;
+      slot = pick_of(own, nxt);
+      if (slot < 0) break;
+      cur = nxt;
+    }
+  }
+  if (lane < d) {
+    a.path_node[(int64_t)r * d + lane] = p_node;
+    a.path_slot[(int64_t)r * d + lane] = p_slot;
+  }
+  if (lane == 0) a.path_len[r] = plen;
+}
+
+template <typename T>
+static void launch_reward_wave(const RewardArgs &a, int nodes, hipStream_t st) {
+  const size_t lds = (size_t)nodes * 20 + (size_t)a.d * a.k * 4;
+  if (nodes <= 64) hipLaunchKernelGGL((k_reward_wave<T, 1>), dim3(a.R), dim3(64), lds, st, a);
+  else hipLaunchKernelGGL((k_reward_wave<T, 2>), dim3(a.R), dim3(64), lds, st, a);
+}
+
 void launch_reward(const RewardArgs &a, hipStream_t st) {
+  if (reward_nodes(a) <= 128) {
+    if (a.dtype == 0) launch_reward_wave<uint16_t>(a, reward_nodes(a), st);
+    else launch_reward_wave<float>(a, reward_nodes(a), st);
+    return;
+  }
   const size_t lds = (size_t)reward_nodes(a) * 12;
   if (a.dtype == 0) hipLaunchKernelGGL(k_reward<uint16_t>, dim3(a.R), dim3(kRewardThreads), lds, st, a);
   else hipLaunchKernelGGL(k_reward<float>, dim3(a.R), dim3(kRewardThreads), lds, st, a);
@@ -429,45 +904,9 @@ void launch_advantage(const AdvArgs &a, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------ surrogate fwd
-template <typename T>
-__global__ void k_ppo_root(PpoFwdArgs a) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= a.R) return;
-  const int d = a.d, k = a.k;
-  const int l = a.path_len[r];
-  const T *dl = static_cast<const T *>(a.draft_logits);
-  const T *rl = static_cast<const T *>(a.ref_logits);
-  double lm = 0.0, lm0 = 0.0;
-  for (int t = 0; t < l; ++t) {
-    const int64_t rt = (int64_t)r * d + t;
-    const int j = a.path_slot[rt];
-    const int tok = min(max(a.sel_tok[(int64_t)r * a.g + a.path_node[rt]], 0), a.V - 1);
-    const int64_t si = stat_index(r, t, j, d, k);
-    const float xc = a.path_logit_cur ? a.path_logit_cur[rt] : Elem<T>::load1(dl + si * a.row_stride + tok);
-    lm += (double)xc - (double)a.draft_lse[si];
-    const double rlse = a.ref_lse_by_step ? (double)a.ref_lse[rt] : (double)a.ref_lse[si];
-    const float xr = a.path_logit_ref ? a.path_logit_ref[rt] : Elem<T>::load1(rl + si * a.row_stride + tok);
-    lm0 += (double)xr - rlse;
-  }
-  const int lden = (l > 1) ? l : 1;
-  const double s = exp((lm - lm0) / lden);
-  const double A = (double)a.adv[r];
-  const double lo = 1.0 - (double)a.eps, hi = 1.0 + (double)a.eps;
-  const double clipped = fmax(lo, fmin(s, hi));
-  const double term = fmin(s * A, clipped * A);
-  const bool passes = (A >= 0.0) ? (s <= hi) : (s >= lo);
-  const int active = (l > 0 && passes) ? 1 : 0;
-  const int K = a.R / a.m;
-  a.logM[r] = (float)lm;
-  a.logM0[r] = (float)lm0;
-  a.ratio[r] = (float)s;
-  a.term[r] = (float)term;
-  a.active[r] = active;
-  a.coef[r] = (float)((double)a.grad_scale * (-A / ((double)a.m * K)) * active * s / lden);
-}
-
-__global__ __launch_bounds__(256) void k_ppo_loss(PpoFwdArgs a) {
-  // single block: group losses (Eq. 12), then their mean; every sum has a fixed shape
+// Group losses (Eq. 12), then their mean, by one workgroup of 256; every sum has a fixed shape.
+template <typename Term>
+__device__ __forceinline__ void group_losses(const PpoFwdArgs &a, Term term) {
   const int K = a.R / a.m;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __shared__ double s_red[256];
@@ -476,7 +915,7 @@ __global__ __launch_bounds__(256) void k_ppo_loss(PpoFwdArgs a) {
     // small groups: one thread per group
     for (int grp = threadIdx.x; grp < K; grp += 256) {
       double sum = 0.0;
-      for (int i = 0; i < a.m; ++i) sum += (double)a.term[grp * a.m + i];
+      for (int i = 0; i < a.m; ++i) sum += (double)term(grp * a.m + i);
       const double lg = -sum / a.m;
       a.loss_group[grp] = (float)lg;
       part += lg;
@@ -485,7 +924,7 @@ __global__ __launch_bounds__(256) void k_ppo_loss(PpoFwdArgs a) {
     // large groups: one wave per group, lane-strided sum and wave reduction
     for (int grp = wave; grp < K; grp += 4) {
       double sum = 0.0;
-      for (int i = lane; i < a.m; i += 64) sum += (double)a.term[grp * a.m + i];
+      for (int i = lane; i < a.m; i += 64) sum += (double)term(grp * a.m + i);
       const double lg = -wave_sum(sum) / a.m;
       if (lane == 0) {
         a.loss_group[grp] = (float)lg;
@@ -500,6 +939,63 @@ __global__ __launch_bounds__(256) void k_ppo_loss(PpoFwdArgs a) {
     __syncthreads();
   }
   if (threadIdx.x == 0) a.loss[0] = (float)(s_red[0] / K);
+}
+
+// 2^shift >= d lanes per root, one per step of the path: a step is three dependent loads (path entry, token and
+// log-sum-exps, logits), which one thread per root paid once per step (1024 roots, two accepted tokens on average:
+// 14.7 us, now 6).  ONE_BLOCK: all roots fit one workgroup, which then also takes the losses.
+template <typename T, bool ONE_BLOCK>
+__global__ __launch_bounds__(256) void k_ppo_root(PpoFwdArgs a, int shift) {
+  const int r = (blockIdx.x * 256 + threadIdx.x) >> shift, t = threadIdx.x & ((1 << shift) - 1);
+  __shared__ float s_term[ONE_BLOCK ? 256 : 1];
+  if (r < a.R) {
+    const int d = a.d, k = a.k;
+    const int l = a.path_len[r];
+    const T *dl = static_cast<const T *>(a.draft_logits);
+    const T *rl = static_cast<const T *>(a.ref_logits);
+    double lm = 0.0, lm0 = 0.0;
+    if (t < l) {
+      const int64_t rt = (int64_t)r * d + t;
+      const int j = a.path_slot[rt];
+      const int tok = min(max(a.sel_tok[(int64_t)r * a.g + a.path_node[rt]], 0), a.V - 1);
+      const int64_t si = stat_index(r, t, j, d, k);
+      const float xc = a.path_logit_cur ? a.path_logit_cur[rt] : Elem<T>::load1(dl + si * a.row_stride + tok);
+      lm = (double)xc - (double)a.draft_lse[si];
+      const double rlse = a.ref_lse_by_step ? (double)a.ref_lse[rt] : (double)a.ref_lse[si];
+      const float xr = a.path_logit_ref ? a.path_logit_ref[rt] : Elem<T>::load1(rl + si * a.row_stride + tok);
+      lm0 = (double)xr - rlse;
+    }
+    for (int off = 1; off < (1 << shift); off <<= 1) {
+      lm += __shfl_xor(lm, off, kWave);
+      lm0 += __shfl_xor(lm0, off, kWave);
+    }
+    if (t == 0) {
+      const int lden = (l > 1) ? l : 1;
+      const double s = exp((lm - lm0) / lden);
+      const double A = (double)a.adv[r];
+      const double lo = 1.0 - (double)a.eps, hi = 1.0 + (double)a.eps;
+      const double clipped = fmax(lo, fmin(s, hi));
+      const double term = fmin(s * A, clipped * A);
+      const bool passes = (A >= 0.0) ? (s <= hi) : (s >= lo);
+      const int active = (l > 0 && passes) ? 1 : 0;
+      const int K = a.R / a.m;
+      a.logM[r] = (float)lm;
+      a.logM0[r] = (float)lm0;
+      a.ratio[r] = (float)s;
+      a.term[r] = (float)term;
+      a.active[r] = active;
+      a.coef[r] = (float)((double)a.grad_scale * (-A / ((double)a.m * K)) * active * s / lden);
+      if (ONE_BLOCK) s_term[r] = (float)term;
+    }
+  }
+  if (ONE_BLOCK) {
+    __syncthreads();
+    group_losses(a, [&](int i) { return s_term[i]; });
+  }
+}
+
+__global__ __launch_bounds__(256) void k_ppo_loss(PpoFwdArgs a) {
+  group_losses(a, [&](int i) { return a.term[i]; });
 }
 
 // (slot, token) pairs whose single logits the fused variant computes as dot products
@@ -531,11 +1027,22 @@ void launch_pairs(const PairArgs &a, int mode, hipStream_t st) {
   hipLaunchKernelGGL(k_pairs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a, mode);
 }
 
-void launch_ppo_fwd(const PpoFwdArgs &a, hipStream_t st) {
-  const int blocks = (a.R + 63) / 64;
-  if (a.dtype == 0) hipLaunchKernelGGL(k_ppo_root<uint16_t>, dim3(blocks), dim3(64), 0, st, a);
-  else hipLaunchKernelGGL(k_ppo_root<float>, dim3(blocks), dim3(64), 0, st, a);
+template <typename T>
+static void launch_ppo_fwd_t(const PpoFwdArgs &a, hipStream_t st) {
+  int shift = 0;
+  while ((1 << shift) < a.d) ++shift;
+  const int64_t threads = (int64_t)a.R << shift;
+  if (threads <= 256) {
+    hipLaunchKernelGGL((k_ppo_root<T, true>), dim3(1), dim3(256), 0, st, a, shift);
+    return;
+  }
+  hipLaunchKernelGGL((k_ppo_root<T, false>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, shift);
   hipLaunchKernelGGL(k_ppo_loss, dim3(1), dim3(256), 0, st, a);
+}
+
+void launch_ppo_fwd(const PpoFwdArgs &a, hipStream_t st) {
+  if (a.dtype == 0) launch_ppo_fwd_t<uint16_t>(a, st);
+  else launch_ppo_fwd_t<float>(a, st);
 }
 
 }  // namespace gto

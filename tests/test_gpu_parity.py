@@ -491,3 +491,52 @@ def test_row_topk_of_adversarial_rows(gpu_device, dtype, V, k, waves):
     Dn = U.logits_np(D)[..., :V]
     U.check_row_stats(U.to_np(ds), O.draft_row_stats(Dn, k), Dn, k)
     U.check_target_stats(U.to_np(ts), O.target_row_stats(Dn))
+
+
+@pytest.mark.parametrize("k,d,g,V", [
+    (8, 2, 64, 600),      # k^2 = 64: one child per lane; 64 kept nodes in one register
+    (9, 6, 65, 600),      # two children per lane, two nodes per lane
+    (11, 5, 128, 600),    # C = 495; 128 nodes, the most a wave takes
+    (12, 4, 129, 600),    # three of four children per lane; 129 nodes: workgroup per root
+    (16, 5, 60, 600),     # k^2 = 256, C = 1040: selection by a workgroup
+    (17, 3, 200, 600),    # expansion by a workgroup
+    (16, 4, 1000, 600),   # C = 784: sixteen keys per lane, more nodes wanted than exist
+    (3, 32, 40, 64),      # deepest tree
+    (1, 3, 2, 16),        # a chain
+])
+@pytest.mark.parametrize("path_mode", [G.GTO_PATH_GREEDY, G.GTO_PATH_MAX_L, G.GTO_PATH_SAMPLED])
+def test_per_root_kernels_at_the_edges_of_their_ranges(gpu_device, k, d, g, V, path_mode):
+    """Expansion, selection, reward and walk from the same statistics, compared with the oracle's logic on those very
+    fp32 statistics: ids, parents and slots bit for bit, the fp64 reward within its fp32 storage."""
+    R = 5
+    gen = torch.Generator().manual_seed(k * 100 + d)
+    cfg = G.make_config(R=R, d=d, k=k, g=g, V=V, dtype=torch.bfloat16, path_mode=path_mode)
+    D = (torch.randn((R, d, k, V), generator=gen) * 2).to(torch.bfloat16).to(gpu_device)
+    T = (D.float() + torch.randn((R, d, k, V), generator=gen).to(gpu_device) * 0.5).to(torch.bfloat16)
+    U01 = torch.rand((R, d, k), generator=gen)
+    ds = G.gto_draft_row_stats(cfg, D, G.alloc_draft_stats(cfg, gpu_device))
+    ts = G.gto_target_row_stats(cfg, T, G.alloc_target_stats(cfg, gpu_device))
+    pool = G.gto_expand_from_stats(cfg, ds, U.alloc_poisoned(G.alloc_pool, cfg, gpu_device))
+    tree = G.gto_select_topg(cfg, pool, U.alloc_poisoned(G.alloc_tree, cfg, gpu_device))
+    rew = U.alloc_poisoned(G.alloc_reward, cfg, gpu_device)
+    rew["accept_u"] = U01.to(gpu_device)
+    G.gto_reward_from_stats(cfg, tree, T, ts, rew)
+    torch.cuda.synchronize()
+    gd, gt, gp, gtr, gr = U.to_np(ds), U.to_np(ts), U.to_np(pool), U.to_np(tree), U.to_np(rew)
+    Tn = U.logits_np(T)
+    op, otree, orew, opath = U.oracle_from_gpu_stats(gd, gt, Tn, d, k, g, 1.0)
+    if path_mode == G.GTO_PATH_MAX_L:
+        opath = O.max_l_path(otree, orew["node_cum"], d)
+    elif path_mode == G.GTO_PATH_SAMPLED:
+        opath = O.sampled_path(otree, Tn, gt["t_lse"].astype(np.float64), U01.numpy().astype(np.float64), d)
+    for n in ("cand_tok", "cand_parent", "cand_depth", "cand_pslot", "cand_slot", "cand_score", "slot_cand"):
+        assert np.array_equal(gp[n], op[n]), n
+    for n in ("sel_cand", "sel_tok", "sel_parent", "sel_depth", "sel_pslot", "sel_slot", "sel_leaf", "n_sel"):
+        assert np.array_equal(gtr[n], otree[n]), n
+    sure = np.ones(R, bool)
+    if path_mode == G.GTO_PATH_SAMPLED:
+        sure = opath["margin"] > 1e-9
+    for n in ("path_len", "path_node", "path_slot"):
+        assert np.array_equal(gr[n][sure], opath[n][sure]), n
+    for n, o in (("node_q", "node_q"), ("node_cum", "node_cum"), ("reward", "reward_lse")):
+        np.testing.assert_allclose(gr[n], orew[o], rtol=1e-6, atol=1e-30)
