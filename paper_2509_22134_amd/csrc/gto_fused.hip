@@ -290,7 +290,10 @@ __device__ __forceinline__ RowSched make_sched(int64_t M, int n_tiles, int G, in
   s.Tr = (int64_t)(s.PR - s.base * G) * s.QC;
   return s;
 }
-__device__ __forceinline__ int64_t rest_begin(const RowSched &s, int x) { return s.Tr * x / s.G; }
+__device__ __forceinline__ int64_t rest_begin(const RowSched &s, int x) {
+  if (s.Tr < (1 << 26)) return (uint32_t)s.Tr * (uint32_t)x / (uint32_t)s.G;     // x <= G <= 16: the usual sizes in 32 bits
+  return s.Tr * x / s.G;
+}
 // number of steps of group x, and its i-th step as (patch row, patch column)
 __device__ __forceinline__ int64_t group_steps(const RowSched &s, int x) {
   return (int64_t)s.base * s.QC + (rest_begin(s, x + 1) - rest_begin(s, x));
@@ -657,18 +660,25 @@ __global__ __launch_bounds__(64) void k_fused_merge(FusedArgs a) {
   const int mblock = (int)(g / FBM);
   const int64_t oi = a.row_list ? (a.out_by_list ? g : (int64_t)a.row_list[g])
                                 : used_slot_index(g, a.rho, a.d, a.kslots);
+  __shared__ int16_t s_slot[16 * kCells];
+  int n_valid = 0;
   float m = neg_inf(), c = kNoRef;
   double s = 0.0;
-  for (int q = lane; q < n_slots; q += 64) {
-    if (!slot_valid(sc, mblock, q)) continue;
+  for (int q0 = 0; q0 < n_slots; q0 += 64) {
+    const int q = q0 + lane;
+    const bool ok = q < n_slots && slot_valid(sc, mblock, q);
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(ok);
+    if (ok) s_slot[n_valid + lanes_below(mask)] = (int16_t)q;
+    n_valid += __builtin_popcountll(mask);
+    if (!ok) continue;
     const float pm = a.part_m[g * n_slots + q];
     if (pm == neg_inf()) continue;
     m = fmaxf(m, pm);
     add_sum(s, c, a.part_s[g * n_slots + q], a.part_c[g * n_slots + q]);
   }
-  const float Mx = wave_max(m);
-  const float C = wave_max(c);
-  const double S = wave_sum(scale_pow2(s, c - C));
+  const float Mx = wave_max_dpp(m);
+  const float C = wave_max_dpp(c);
+  const double S = wave_sum_dpp(scale_pow2(s, c - C));
   const double lse = (double)Mx + kLn2 * (((double)C - (double)Mx * (double)kLog2e) + log2(S));
   if (lane == 0) {
     if (a.row_max) a.row_max[oi] = Mx;
@@ -677,11 +687,13 @@ __global__ __launch_bounds__(64) void k_fused_merge(FusedArgs a) {
   if (a.top_tok == nullptr) return;
   const float *pv = a.part_v + g * n_slots * ktop;
   const int32_t *pi = a.part_i + g * n_slots * ktop;
-  const int total = n_slots * ktop;
+  const int total = n_valid * ktop;
+  __builtin_amdgcn_wave_barrier();
   auto fetch = [&](int j, float &v, int &id) {
-    const bool ok = j < total && slot_valid(sc, mblock, j / ktop);
-    v = ok ? pv[j] : neg_inf();
-    id = ok ? pi[j] : kNoId;
+    const int q = min(j, total - 1) / ktop;
+    const int at = s_slot[q] * ktop + (min(j, total - 1) - q * ktop);
+    v = (j < total) ? pv[at] : neg_inf();
+    id = (j < total) ? pi[at] : kNoId;
   };
   float cv[kMergeReg];
   int ci[kMergeReg];
@@ -735,7 +747,7 @@ __device__ __forceinline__ double sum_others(const double *part_s, int64_t g, co
   double tot = 0.0;
   for (int c = lane_id(); c < n_slots; c += 64)
     if (slot_valid(sc, (int)(g / FBM), c)) tot += part_s[g * n_slots + c];
-  return wave_sum(tot);
+  return wave_sum_dpp(tot);
 }
 
 // Backward fix-up, one wave per processed row: the accepted token's entry is coef times the sum
@@ -752,72 +764,70 @@ __global__ __launch_bounds__(64) void k_fused_bwd_fixup(FusedArgs a) {
     a.grad_rows[(int64_t)pidx * a.V + tok] = (float)((double)a.coef[rr] * tot);
 }
 
-// Ordered compaction (single workgroup): the (root, step) pairs that carry a gradient, their
-// hidden-row slots, and grad_slot for every pair.
-__global__ __launch_bounds__(1024) void k_bwd_rows(BwdRowsArgs a) {
+// Ordered compaction by a single workgroup of 1024: wave w takes the w-th part of the entries, counts them, learns its
+// place from the other waves' counts and writes; valid(p), emit(p, position); returns the total in every thread.
+// (65 536 flags with a scan over the workgroup per 1024 entries: 62 us.)
+// kU: entries per lane and trip, independent loads.
+template <int kU, typename Valid, typename Emit>
+__device__ __forceinline__ int compact_ordered(int n, Valid valid, Emit emit) {
   __shared__ int s_wave[16];
-  __shared__ int s_base;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) s_base = 0;
-  __syncthreads();
-  const int n = a.R * a.d;
-  for (int p0 = 0; p0 < n; p0 += 1024) {
-    const int p = p0 + tid;
-    bool valid = false;
-    int j = -1;
-    if (p < n) {
-      j = a.path_slot[p];
-      valid = (j >= 0) && (a.coef[p / a.d] != 0.f);
-      a.grad_slot[p] = valid ? j : -1;
-    }
-    const uint64_t bal = __builtin_amdgcn_ballot_w64(valid);
-    const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) s_wave[wave] = __builtin_popcountll(bal);
-    __syncthreads();
-    int off = s_base;
-    for (int w = 0; w < wave; ++w) off += s_wave[w];
-    if (valid) {
-      const int r = p / a.d, t = p - r * a.d;
-      a.list_p[off + before] = p;
-      a.list_slot[off + before] = (int)stat_index(r, t, j, a.d, a.k);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      int tot = 0;
-      for (int w = 0; w < 16; ++w) tot += s_wave[w];
-      s_base += tot;
-    }
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int part = ((n + 1023) / 1024) * 64;
+  const int p0 = min(wave * part, n), p1 = min(p0 + part, n);
+  auto trip = [&](int p, uint64_t (&mask)[kU]) {
+    bool v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = valid(min(p + u * 64 + lane, n - 1));
+#pragma unroll
+    for (int u = 0; u < kU; ++u) mask[u] = __builtin_amdgcn_ballot_w64(v[u] && p + u * 64 + lane < p1);
+  };
+  int cnt = 0;
+  uint64_t mask[kU];
+  for (int p = p0; p < p1; p += kU * 64) {
+    trip(p, mask);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) cnt += __builtin_popcountll(mask[u]);
   }
-  if (tid == 0) *a.count = s_base;
+  if (lane == 0) s_wave[wave] = cnt;
+  __syncthreads();
+  int at = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    at += (w < wave) ? s_wave[w] : 0;
+    total += s_wave[w];
+  }
+  for (int p = p0; p < p1; p += kU * 64) {
+    if (p1 - p0 > kU * 64) trip(p, mask);    // (a single trip's masks are still there)
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      if ((mask[u] >> lane) & 1ull) emit(p + u * 64 + lane, at + lanes_below(mask[u]));
+      at += __builtin_popcountll(mask[u]);
+    }
+  }
+  return total;
 }
 
-// Ordered compaction (single workgroup) of the slots whose flag is set: list of slot indices + count.
+// The (root, step) pairs that carry a gradient, their hidden-row slots, and grad_slot for every pair.
+__global__ __launch_bounds__(1024) void k_bwd_rows(BwdRowsArgs a) {
+  const int total = compact_ordered<4>(
+      a.R * a.d,
+      [&](int p) {
+        const int j = (a.coef[p / a.d] != 0.f) ? max(a.path_slot[p], -1) : -1;
+        a.grad_slot[p] = j;                  // (by every trip that looks: the same value)
+        return j >= 0;
+      },
+      [&](int p, int at) {
+        const int r = p / a.d, t = p - r * a.d;
+        a.list_p[at] = p;
+        a.list_slot[at] = (int)stat_index(r, t, a.path_slot[p], a.d, a.k);
+      });
+  if (threadIdx.x == 0) *a.count = total;
+}
+
+// The slots whose flag is set: list of slot indices + count.
 __global__ __launch_bounds__(1024) void k_compact_flags(const int32_t *flags, int n, int32_t *list, int32_t *count) {
-  __shared__ int s_wave[16];
-  __shared__ int s_base;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) s_base = 0;
-  __syncthreads();
-  for (int p0 = 0; p0 < n; p0 += 1024) {
-    const int p = p0 + tid;
-    const bool valid = (p < n) && (flags[p] != 0);
-    const uint64_t bal = __builtin_amdgcn_ballot_w64(valid);
-    const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) s_wave[wave] = __builtin_popcountll(bal);
-    __syncthreads();
-    int off = s_base;
-    for (int w = 0; w < wave; ++w) off += s_wave[w];
-    if (valid) list[off + before] = p;
-    __syncthreads();
-    if (tid == 0) {
-      int tot = 0;
-      for (int w = 0; w < 16; ++w) tot += s_wave[w];
-      s_base += tot;
-    }
-    __syncthreads();
-  }
-  if (tid == 0) *count = s_base;
+  const int total = compact_ordered<16>(n, [&](int p) { return flags[p] != 0; }, [&](int p, int at) { list[at] = p; });
+  if (threadIdx.x == 0) *count = total;
 }
 
 void launch_compact_flags(const int32_t *flags, int n, int32_t *list, int32_t *count, hipStream_t st) {
@@ -941,10 +951,21 @@ __global__ __launch_bounds__(256) void k_fused_dh_reduce(FusedDhArgs a) {
   const int64_t M = min((int64_t)*a.m_dev, a.M);
   const double others = sum_others(a.part_s, g, make_sched(M, a.n_tiles, a.groups, a.patch_rows, a.patch_cols));
   const float ctok = (float)((double)coef * others);
-  for (int h = threadIdx.x; h < a.hidden_dim; h += 256) {
-    float sum = 0.f;
-    for (int s = 0; s < a.n_splits; ++s) sum += a.partial[((int64_t)s * a.M + g) * a.hidden_dim + h];
-    a.dh_rows[(int64_t)pidx * a.hidden_dim + h] = __builtin_fmaf(ctok, Elem<uint16_t>::load1(wrow + h), sum);
+  // four columns a thread (hidden_dim is a multiple of 64), eight splits at a time
+  for (int h = threadIdx.x * 4; h < a.hidden_dim; h += 1024) {
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < a.n_splits; s0 += 8) {
+      f32x4 q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        q[u] = *reinterpret_cast<const f32x4 *>(a.partial + ((int64_t)min(s0 + u, a.n_splits - 1) * a.M + g) * a.hidden_dim + h);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < a.n_splits) sum += q[u];
+    }
+    float *o = a.dh_rows + (int64_t)pidx * a.hidden_dim + h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(ctok, Elem<uint16_t>::load1(wrow + h + e), sum[e]);
   }
 }
 
