@@ -333,8 +333,7 @@ int check_fused(const gto_config *c, const void *hidden, int hidden_dim, const v
 
 // Launch geometry of the row pass (see the work distribution in gto_fused.hip): `groups` groups of 32 workgroups.
 // By default 8 groups, one per XCD and one workgroup per compute unit, with a patch shape that follows the row
-// count (8 x 4 for many rows: it takes the same time as 4 x 8, streams the head half as often, fetches a quarter
-// less from the fabric and leaves half as many partial results).
+// and column counts.
 FusedPlan fused_plan(const gto_config *c, int64_t M, int ktop) {
   FusedPlan p{};
   p.M = M;
@@ -342,7 +341,7 @@ FusedPlan fused_plan(const gto_config *c, int64_t M, int ktop) {
   p.groups = c->fused_groups > 0 ? c->fused_groups : 8;
   p.patch_rows = c->fused_layout == 0 ? 0 : 4;
   p.patch_cols = c->fused_layout == 0 ? 0 : 8;
-  const size_t rows = (size_t)gto::fused_partials(M, p.groups, p.patch_rows, p.patch_cols);
+  const size_t rows = (size_t)gto::fused_partials(M, p.n_tiles, p.groups, p.patch_rows, p.patch_cols);
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   p.off_s = 0;
   p.off_m = up(p.off_s + rows * sizeof(double));

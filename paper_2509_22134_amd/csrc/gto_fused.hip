@@ -87,22 +87,21 @@ __device__ __forceinline__ void list_insert(float (&v)[KT], int (&id)[KT], float
 //
 // What bounds it: the matrix pipe, as long as nothing else stands in its way.  One wave per SIMD that issues
 // fragment reads and loads between its MFMAs stalls the pipe whenever one of those instructions is held up
-// (measured: 0.66 busy, 110 ms for 58 368 x 8192 x 128 256).  So two waves share a SIMD and take turns: the waves of group 0 (wm = 0) and of group 1
-// are half a phase apart, and between two barriers one group issues 16 MFMAs (256 matrix-pipe cycles) while the
-// other reads fragments and requests loads for its next 16.  A slab is four such phases, one per quadrant of the
-// wave's tile, in an order in which each quadrant shares an operand half with the one before:
-//     phase   MFMA quadrant      fragments read before it      load requested before it (slab s + 2)
-//       0     A0 x B0            A0 (8 reads)                  B0
-//       1     A0 x B1            B1 (4)                        A0
-//       2     A1 x B1            A1 (8)                        B1
-//       3     A1 x B0            B0 of slab s + 1 (4)          A1
-// (A0 / A1: the first and second 64 rows of each row half; B0 / B1: the first and second 32 columns of each column
-// wave.)  A quarter of a stage is requested again as soon as both groups have read it, so two stages of 64 KB keep
-// every load in flight for a slab and a half (about 3000 clocks).  Every phase ends its reading part with
-// `vmcnt(12)`: at most the six newest requests (two instructions each) are still out, which is exactly what the
-// next phase does not read; the barrier extends that to the other waves' shares.
-// Measured: 58 368 x 8192 x 128 256 with the statistics epilogue in 89.4 ms (1.37 PFLOP/s; 110.0 ms with one wave
-// per SIMD and 32x32x16 tiles), the writing passes 2.96 ms (3.80), 2.28 ms (2.99).
+// (measured: 0.66 busy, 110 ms for 58 368 x 8192 x 128 256).  So two waves share a SIMD and take turns: the waves of
+// group 0 (wm = 0) and of group 1 are half a phase apart, and between two barriers one group issues 32 MFMAs (512
+// matrix-pipe cycles) while the other reads fragments and requests loads for its next 32.  A slab is two such phases:
+//     phase   MFMAs       fragments read before them    loads requested before them
+//       0     A0 x B      B (8 reads), A0 (8)           A1 of slab s + 1
+//       1     A1 x B      A1 (8)                        B, A0 of slab s + 2
+// (A0 / A1: the first and second 64 rows of each row half; B: the wave's 64 columns.)  A part of a stage is requested
+// again as soon as both groups have read it, so two stages of 64 KB keep every load in flight for one and a half
+// slabs (about 3000 clocks).  Every phase ends its reading part with `vmcnt(8)`: the eight newest load instructions
+// are exactly what the next phase does not read; the barrier extends that to the other waves' shares.
+// Measured with the statistics epilogue: 16 359 x 8192 x 128 256 in 24.4 ms (1.41 PFLOP/s at 1.60 GHz with the matrix
+// pipe 0.83 busy: the power limit holds the clock; the library's GEMM reaches 1.55 in the same process), 58 368 rows
+// in 89 to 93 ms.  Phases of 16 MFMAs, four a slab, lose more to the barriers (0.77 busy at 1.80 GHz): 2.5 % slower
+// in a run of 25 ms, the same in one of 90.  Four waves of 128 x 128 with accumulators pinned to the accumulation
+// registers read a third less LDS but reach 1.31 PFLOP/s without an epilogue.
 struct Slab {
   unsigned wA, wB;               // LDS byte address of this wave's share of A0 / B0 in stage 0
   const unsigned char *ldsb;     // the stages
@@ -117,17 +116,17 @@ __device__ __forceinline__ void end_of_reads() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int I0, int J0>
-__device__ __forceinline__ void quadrant(f32x4 (&acc)[8][4], const bf16x8 (&fa)[2][4], const bf16x8 (&fb)[2][2]) {
+template <int I0>
+__device__ __forceinline__ void half_tile(f32x4 (&acc)[8][4], const bf16x8 (&fa)[2][4], const bf16x8 (&fb)[2][4]) {
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = (i & 1) ? 1 - jj : jj;        // one operand changes per MFMA
-        acc[I0 + i][J0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[I0 + i][J0 + j], 0, 0, 0);
+      for (int jj = 0; jj < 4; ++jj) {
+        const int j = (i & 1) ? 3 - jj : jj;        // one operand changes per MFMA
+        acc[I0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[I0 + i][j], 0, 0, 0);
       }
   __builtin_amdgcn_s_setprio(0);
   __builtin_amdgcn_sched_barrier(0);
@@ -152,28 +151,26 @@ __device__ __forceinline__ void request(unsigned lds_addr, const uint16_t *&p0, 
   p1 += FBK;
 }
 
-// One slab.  LOAD: slab s + 2 exists and is requested.  NEXT: slab s + 1 exists.  V0..V3: outstanding load
-// instructions allowed at the end of each phase's reads.  x holds B0 on entry; y receives B1, then slab s + 1's B0.
-template <bool LOAD, bool NEXT, int V0, int V1, int V2, int V3>
-__device__ __forceinline__ void slab_step(f32x4 (&acc)[8][4], bf16x8 (&fa)[2][4], bf16x8 (&x)[2][2], bf16x8 (&y)[2][2],
-                                          const Slab &r, const uint16_t *(&ap)[4], const uint16_t *(&bp)[4], int stage) {
+// One slab.  LOAD_A1: slab s + 1 exists and the second half of its row operand is requested.  LOAD: slab s + 2 exists
+// and the rest of it is requested.  V0, V1: outstanding load instructions allowed at the end of each phase's reads.
+template <bool LOAD_A1, bool LOAD, int V0, int V1>
+__device__ __forceinline__ void slab_step(f32x4 (&acc)[8][4], const Slab &r, const uint16_t *(&ap)[4],
+                                          const uint16_t *(&bp)[4], int stage) {
   const int off = stage * FSTAGE_B, nxt = FSTAGE_B - off;
+  bf16x8 fa[2][4], fb[2][4];
+  read_frags<4>(fb, r.ldsb, r.fB, off);
   read_frags<4>(fa, r.ldsb, r.fA, off);
-  if (LOAD) request(r.wB + off, bp[0], bp[1]);
+  if (LOAD_A1) request(r.wA + nxt + 64 * FROWB, ap[2], ap[3]);
   end_of_reads<V0>();
-  quadrant<0, 0>(acc, fa, x);
-  read_frags<2>(y, r.ldsb, r.fB, off + 32 * FROWB);
-  if (LOAD) request(r.wA + off, ap[0], ap[1]);
-  end_of_reads<V1>();
-  quadrant<0, 2>(acc, fa, y);
+  half_tile<0>(acc, fa, fb);
   read_frags<4>(fa, r.ldsb, r.fA, off + 64 * FROWB);
-  if (LOAD) request(r.wB + off + 32 * FROWB, bp[2], bp[3]);
-  end_of_reads<V2>();
-  quadrant<4, 2>(acc, fa, y);
-  if (NEXT) read_frags<2>(y, r.ldsb, r.fB, nxt);
-  if (LOAD) request(r.wA + off + 64 * FROWB, ap[2], ap[3]);
-  end_of_reads<V3>();
-  quadrant<4, 0>(acc, fa, x);
+  if (LOAD) {
+    request(r.wB + off, bp[0], bp[1]);
+    request(r.wA + off, ap[0], ap[1]);
+    request(r.wB + off + 32 * FROWB, bp[2], bp[3]);
+  }
+  end_of_reads<V1>();
+  half_tile<4>(acc, fa, fb);
 }
 
 // Which rows of the two operands this lane fetches: load i of quarter A0 is tile row a_row(i), of A1 a_row(i) + 64;
@@ -204,43 +201,23 @@ __device__ __forceinline__ void tile_mainloop(f32x4 (&acc)[8][4], uint16_t *lds,
   r.fA = wm * 128 * FROWB + fl;
   r.fB = FOP_B + wn * 64 * FROWB + fl;
   __syncthreads();                           // the previous user of the stages (an epilogue's staging area) is done
-#pragma unroll
-  for (int s_ = 0; s_ < 2; ++s_)
-    if (s_ < n_slabs) {
-      request(r.wB + s_ * FSTAGE_B, bp[0], bp[1]);
-      request(r.wA + s_ * FSTAGE_B, ap[0], ap[1]);
-      request(r.wB + s_ * FSTAGE_B + 32 * FROWB, bp[2], bp[3]);
-      request(r.wA + s_ * FSTAGE_B + 64 * FROWB, ap[2], ap[3]);
-    }
-  bf16x8 fa[2][4], x[2][2], y[2][2];
-  if (n_slabs > 1) end_of_reads<12>();       // B0 and A0 of slab 0 have landed
-  else end_of_reads<4>();
-  read_frags<2>(x, r.ldsb, r.fB, 0);
+  request(r.wB, bp[0], bp[1]);
+  request(r.wA, ap[0], ap[1]);
+  request(r.wB + 32 * FROWB, bp[2], bp[3]);
+  request(r.wA + 64 * FROWB, ap[2], ap[3]);
+  if (n_slabs > 1) {
+    request(r.wB + FSTAGE_B, bp[0], bp[1]);
+    request(r.wA + FSTAGE_B, ap[0], ap[1]);
+    request(r.wB + FSTAGE_B + 32 * FROWB, bp[2], bp[3]);
+    end_of_reads<8>();                       // all of slab 0 but A1 has landed
+  } else {
+    end_of_reads<2>();
+  }
   if (wm) __builtin_amdgcn_s_barrier();      // group 1 runs half a phase behind group 0
   int s = 0;
-  for (; s + 3 < n_slabs; s += 2) {          // whole pairs of slabs whose second successors exist
-    slab_step<true, true, 12, 12, 12, 12>(acc, fa, x, y, r, ap, bp, 0);
-    slab_step<true, true, 12, 12, 12, 12>(acc, fa, y, x, r, ap, bp, 1);
-  }
-  // two or three slabs are left (one if n_slabs is 1); s is even
-  int st = 0;
-  if (s + 2 < n_slabs) {
-    slab_step<true, true, 12, 12, 12, 12>(acc, fa, x, y, r, ap, bp, 0);
-    st = 1;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) x[h][t] = y[h][t];
-  }
-  if (n_slabs > 1) {
-    slab_step<false, true, 10, 8, 6, 4>(acc, fa, x, y, r, ap, bp, st);
-    st ^= 1;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) x[h][t] = y[h][t];
-  }
-  slab_step<false, false, 2, 0, 0, 0>(acc, fa, x, y, r, ap, bp, st);
+  for (; s + 2 < n_slabs; ++s) slab_step<true, true, 8, 8>(acc, r, ap, bp, s & 1);
+  if (n_slabs > 1) slab_step<true, false, 8, 2>(acc, r, ap, bp, s++ & 1);
+  slab_step<false, false, 0, 0>(acc, r, ap, bp, s & 1);
   if (!wm) __builtin_amdgcn_s_barrier();
 }
 
@@ -261,16 +238,25 @@ __device__ __forceinline__ void tile_mainloop(f32x4 (&acc)[8][4], uint16_t *lds,
 //   - Every group gets the same number of steps to within one, whatever the shape: no tail of idle
 //     compute units, and nothing depends on the row count being known on the host (a launch over a
 //     device-side row list reads its count here).
-//   - The patch follows the number of row blocks: at most 8 rows high, and no higher than an even split of the
-//     row blocks needs (9 row blocks: two patch rows of 5, not of 8), as wide as fits the group.  With a fixed
-//     8 x 4 patch one row block kept an eighth of the chip busy and two a quarter (456 rows x 8192 x 128 256:
-//     2.37 ms, now 0.8 to 1.1; 1024 rows: 2.28 ms, now 1.6).
+//   - The patch follows the numbers of row blocks and column tiles: the shape pr x (32 / pr) that covers them in the
+//     fewest steps of a group, the tallest among equals.  With a fixed 8 x 4 patch one row block kept an eighth of the
+//     chip busy and two a quarter (456 rows x 8192 x 128 256: 2.37 ms, now 0.8 to 1.1; 1024 rows: 2.28 ms, now 1.6),
+//     and 57 row blocks left seven eighths of the eighth patch row empty (24.0 ms with pr = 8, 23.1 with 4).  A step
+//     takes about the same time with pr = 2, 4 and 8 (64 row blocks: 24.3, 24.3, 24.4 ms), so a lower patch has to
+//     save 2.5 %; with pr = 1 nobody shares a column tile, which costs a tenth, in the passes that write a quarter.
+//     Many row blocks waste little either way and stay at pr >= 4, which bounds the partial results.
 constexpr int kCells = 32;        // workgroups of a group
-__host__ __device__ inline void patch_shape(int64_t m_blocks, int &pr, int &pc) {
+constexpr int kFewBlocks = 16;    // up to here any height is considered
+__host__ __device__ inline void patch_shape(int64_t m_blocks, int64_t n_tiles, int groups, int &pr, int &pc) {
   const int64_t mb = m_blocks < 1 ? 1 : m_blocks;
-  const int64_t rows = (mb + 7) / 8;
-  pr = (int)((mb + rows - 1) / rows);
-  pc = kCells / pr;
+  int64_t best = 0;
+  for (int h = 8; h >= (mb <= kFewBlocks ? 1 : 4); --h) {
+    if (h > mb) continue;
+    const int w = kCells / h;
+    const int64_t steps = (((mb + h - 1) / h) * ((n_tiles + w - 1) / w) + groups - 1) / groups;
+    const int64_t cost = steps * ((h == 1 && mb > 1) ? 50 : h <= 4 ? 41 : 40);
+    if (best == 0 || cost < best) { best = cost; pr = h; pc = w; }
+  }
 }
 struct RowSched {
   int m_blocks, n_tiles, PR, QC, pr, pc, G;
@@ -281,7 +267,7 @@ struct RowSched {
 __device__ __forceinline__ RowSched make_sched(int64_t M, int n_tiles, int G, int pr, int pc) {
   RowSched s;
   s.m_blocks = (int)((M + FBM - 1) / FBM);
-  if (pr == 0) patch_shape(s.m_blocks, pr, pc);
+  if (pr == 0) patch_shape(s.m_blocks, n_tiles, G, pr, pc);
   s.n_tiles = n_tiles;
   s.pr = pr; s.pc = pc; s.G = G;
   s.PR = (s.m_blocks + pr - 1) / pr;
@@ -975,14 +961,14 @@ static void set_lds_attr(K kern) {
                             (int)kFusedLdsBytes);
 }
 
-int64_t fused_partials(int64_t rows, int groups, int pr, int pc) {
+int64_t fused_partials(int64_t rows, int n_tiles, int groups, int pr, int pc) {
   if (pr != 0) return rows * groups * pc;
-  int64_t most = 0;
-  for (int64_t mb = 1; mb <= 64 && (mb - 1) * FBM < rows; ++mb) {      // from 19 row blocks on the patch is 4 wide
-    patch_shape(mb, pr, pc);
+  int64_t most = rows * (kCells / 4);                     // beyond kFewBlocks the patch is at most eight tiles wide
+  for (int64_t mb = 1; mb <= kFewBlocks && (mb - 1) * FBM < rows; ++mb) {
+    patch_shape(mb, n_tiles, groups, pr, pc);
     most = std::max(most, std::min(rows, mb * FBM) * pc);
   }
-  return groups * std::max(most, rows * 4);
+  return groups * most;
 }
 
 static int fused_grid(const FusedArgs &a) { return a.groups * kCells; }

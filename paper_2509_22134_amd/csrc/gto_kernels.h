@@ -159,7 +159,7 @@ struct PairArgs {
   int32_t *tok;
 };
 // partial results (of one row and slot each) that a row pass over at most `rows` rows may leave
-int64_t fused_partials(int64_t rows, int groups, int patch_rows, int patch_cols);
+int64_t fused_partials(int64_t rows, int n_tiles, int groups, int patch_rows, int patch_cols);
 void launch_pairs(const PairArgs &a, int mode, hipStream_t st);
 void launch_fused_rows(const FusedArgs &a, hipStream_t st);
 void launch_fused_bwd_fixup(const FusedArgs &a, hipStream_t st);
