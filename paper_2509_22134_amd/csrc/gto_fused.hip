@@ -861,12 +861,16 @@ __global__ __launch_bounds__(FTHREADS, 2) void k_fused_dh(FusedDhArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
+  // Workgroup i runs on XCD i % 8: with eight splits an XCD keeps to one k range, and the row blocks of a column block
+  // run next to each other, so that its L2 serves a head tile to all of them (910 rows x 8192: 3.17 ms with the
+  // column blocks next to each other, now 2.75).
+  const int64_t M = min((int64_t)*a.m_dev, a.M);
+  const int m_blocks = (int)((M + FBM - 1) / FBM);
   const int split = blockIdx.x % a.n_splits;
   const int rest = blockIdx.x / a.n_splits;
-  const int hblock = rest % a.h_blocks, mblock = rest / a.h_blocks;
-  const int64_t M = min((int64_t)*a.m_dev, a.M);
+  if (rest >= m_blocks * a.h_blocks) return;
+  const int mblock = rest % m_blocks, hblock = rest / m_blocks;
   const int64_t row0 = (int64_t)mblock * FBM;
-  if (row0 >= M) return;
   const int nks = (int)(a.plane_pitch / FBK);                 // slabs per plane (the last one may be half padding)
   const int s0 = split * a.slabs_per_split;
   const int s1 = min(s0 + a.slabs_per_split, 2 * nks);
