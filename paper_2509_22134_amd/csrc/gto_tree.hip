@@ -11,6 +11,8 @@
 // inverted index): keys are unique, so (score descending, index ascending) is realised exactly and
 // deterministically whether a rank is found by counting the keys that beat mine (expansion: k^2
 // keys per level) or by sorting (top-g: C keys).
+#include <type_traits>
+
 #include "gto_device.h"
 #include "gto_kernels.h"
 
@@ -363,14 +365,19 @@ __device__ __forceinline__ void bitonic_sort(double (&key)[NPL], int lane) {
   bitonic_stage<NPL, SIZE, SIZE / 2>(key, lane);
   if constexpr (SIZE < 64 * NPL) bitonic_sort<NPL, SIZE * 2>(key, lane);
 }
-// Dynamic LDS: C ranks (2 B), n_keep candidates (2 B), n_keep leaf flags, d * k need flags (1 B each).
-template <int NPL>
+// Few kept nodes (SORT < NPL: n_keep <= 64 SORT): a threshold that n_keep to 64 SORT of the scores reach is bisected
+// first, some ten rounds of compares and bit counts, and only those are sorted (1024 roots, 60 of 510: 12 us with all
+// keys sorted, 9 so; 4 roots 9 us and 6).  More ties than that at the threshold: all keys are sorted.
+// Dynamic LDS: 64 SORT keys (8 B, SORT < NPL), C ranks (2 B), n_keep candidates (2 B), n_keep leaf flags, d * k need
+// flags (1 B each).
+template <int NPL, int SORT>
 __global__ __launch_bounds__(64) void k_select_wave(SelectArgs a) {
   const int r = blockIdx.x, lane = threadIdx.x;
   const int C = a.C, g = a.g;
   const int n_keep = (g < C) ? g : C;
   extern __shared__ __align__(16) unsigned char s_dyn[];
-  int16_t *s_rank = reinterpret_cast<int16_t *>(s_dyn);
+  double *s_few = reinterpret_cast<double *>(s_dyn);
+  int16_t *s_rank = reinterpret_cast<int16_t *>(s_few + (SORT < NPL ? 64 * SORT : 0));
   int16_t *s_sel = s_rank + C;
   unsigned char *s_leaf = reinterpret_cast<unsigned char *>(s_sel + n_keep);
   unsigned char *s_need = s_leaf + n_keep;
@@ -386,15 +393,57 @@ __global__ __launch_bounds__(64) void k_select_wave(SelectArgs a) {
   for (int c = lane; c < C; c += 64) s_rank[c] = 0x7fff;
   for (int i = lane; i < n_keep; i += 64) s_leaf[i] = 1;
   for (int i = lane; i < a.d * a.k; i += 64) s_need[i] = 0;
-  bitonic_sort<NPL>(key, lane);
+  auto emit = [&](auto &sorted, auto npl) {
 #pragma unroll
-  for (int e = 0; e < NPL; ++e) {
-    const int i = lane * NPL + e;
-    if (i < n_keep) {
-      const int c = sort_index(key[e]);
-      s_rank[c] = (int16_t)i;
-      s_sel[i] = (int16_t)c;
+    for (int e = 0; e < decltype(npl)::value; ++e) {
+      const int i = lane * decltype(npl)::value + e;
+      if (i < n_keep) {
+        const int c = sort_index(sorted[e]);
+        s_rank[c] = (int16_t)i;
+        s_sel[i] = (int16_t)c;
+      }
     }
+  };
+  bool few = SORT < NPL;
+  if constexpr (SORT < NPL) {
+    uint32_t o[NPL];                              // the scores' bits; padding: 0
+#pragma unroll
+    for (int e = 0; e < NPL; ++e) o[e] = (uint32_t)((uint64_t)__double_as_longlong(key[e]) >> 20);
+    uint32_t lo = 0u, hi = 0xffffffffu;           // count(>= lo) >= n_keep > count(>= hi)
+    int cnt = 64 * NPL;
+    while (cnt > 64 * SORT && hi - lo > 1u) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      int c = 0;
+#pragma unroll
+      for (int e = 0; e < NPL; ++e) c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(o[e] >= mid));
+      if (c >= n_keep) {
+        lo = mid;
+        cnt = c;
+      } else {
+        hi = mid;
+      }
+    }
+    few = cnt <= 64 * SORT;
+    if (few) {
+      int at = 0;
+#pragma unroll
+      for (int e = 0; e < NPL; ++e) {
+        const bool on = o[e] >= lo;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(on);
+        if (on) s_few[at + lanes_below(mask)] = key[e];
+        at += __builtin_popcountll(mask);
+      }
+      __builtin_amdgcn_wave_barrier();
+      double best[SORT];
+#pragma unroll
+      for (int e = 0; e < SORT; ++e) best[e] = (e * 64 + lane < cnt) ? s_few[e * 64 + lane] : 1.0;
+      bitonic_sort<SORT>(best, lane);
+      emit(best, std::integral_constant<int, SORT>{});
+    }
+  }
+  if (!few) {
+    bitonic_sort<NPL>(key, lane);
+    emit(key, std::integral_constant<int, NPL>{});
   }
   __builtin_amdgcn_wave_barrier();
   for (int i = lane; i < n_keep; i += 64) {
@@ -432,18 +481,29 @@ __global__ __launch_bounds__(64) void k_select_wave(SelectArgs a) {
   if (lane == 0) a.n_sel[r] = n_keep;
 }
 
+template <int NPL, int SORT>
+static void launch_select_wave(const SelectArgs &a, int n_keep, hipStream_t st) {
+  const size_t lds = (SORT < NPL ? 64 * SORT * sizeof(double) : 0) + (size_t)a.C * 2 + (size_t)n_keep * 3 + (size_t)a.d * a.k;
+  hipLaunchKernelGGL((k_select_wave<NPL, SORT>), dim3(a.R), dim3(64), lds, st, a);
+}
+template <int NPL>
+static void launch_select_wave_n(const SelectArgs &a, int n_keep, int sort, hipStream_t st) {
+  if (sort == 1) launch_select_wave<NPL, 1>(a, n_keep, st);
+  else if (sort == 2) launch_select_wave<NPL, 2>(a, n_keep, st);
+  else launch_select_wave<NPL, NPL>(a, n_keep, st);
+}
+
 void launch_select(const SelectArgs &a, hipStream_t st) {
   int n_pad = 2;
   while (n_pad < a.C) n_pad <<= 1;
   const int n_keep = (a.g < a.C) ? a.g : a.C;
   if (n_pad <= 1024) {
-    const size_t lds_wave = (size_t)a.C * 2 + (size_t)n_keep * 3 + (size_t)a.d * a.k;
-    const dim3 grid(a.R), block(64);
-    if (n_pad <= 64) hipLaunchKernelGGL(k_select_wave<1>, grid, block, lds_wave, st, a);
-    else if (n_pad <= 128) hipLaunchKernelGGL(k_select_wave<2>, grid, block, lds_wave, st, a);
-    else if (n_pad <= 256) hipLaunchKernelGGL(k_select_wave<4>, grid, block, lds_wave, st, a);
-    else if (n_pad <= 512) hipLaunchKernelGGL(k_select_wave<8>, grid, block, lds_wave, st, a);
-    else hipLaunchKernelGGL(k_select_wave<16>, grid, block, lds_wave, st, a);
+    const int sort = (n_keep <= 64) ? 1 : (n_keep <= 128) ? 2 : 16;
+    if (n_pad <= 64) launch_select_wave<1, 1>(a, n_keep, st);
+    else if (n_pad <= 128) sort == 1 ? launch_select_wave<2, 1>(a, n_keep, st) : launch_select_wave<2, 2>(a, n_keep, st);
+    else if (n_pad <= 256) launch_select_wave_n<4>(a, n_keep, sort, st);
+    else if (n_pad <= 512) launch_select_wave_n<8>(a, n_keep, sort, st);
+    else launch_select_wave_n<16>(a, n_keep, sort, st);
     return;
   }
   const size_t lds = (size_t)n_pad * 8 + (size_t)a.C * 4 + (size_t)n_keep + (size_t)a.d * a.k;

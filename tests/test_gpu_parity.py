@@ -540,3 +540,32 @@ def test_per_root_kernels_at_the_edges_of_their_ranges(gpu_device, k, d, g, V, p
         assert np.array_equal(gr[n][sure], opath[n][sure]), n
     for n, o in (("node_q", "node_q"), ("node_cum", "node_cum"), ("reward", "reward_lse")):
         np.testing.assert_allclose(gr[n], orew[o], rtol=1e-6, atol=1e-30)
+
+
+@pytest.mark.parametrize("k,d,g", [(10, 6, 60), (10, 6, 64), (10, 6, 65), (10, 6, 128), (10, 6, 129), (12, 6, 30)])
+@pytest.mark.parametrize("distinct", [1, 3, 70, 100000])
+def test_selection_with_ties(gpu_device, k, d, g, distinct):
+    """Selection from pools whose scores take few distinct values (more ties at the cut than a wave has lanes), -inf
+    and both zeros among them: the order is (score descending, index ascending) throughout."""
+    R = 4
+    cfg = G.make_config(R=R, d=d, k=k, g=g, V=1000, dtype=torch.bfloat16)
+    gen = torch.Generator().manual_seed(g * 7 + distinct)
+    C = cfg.C
+    score = -torch.randint(0, distinct, (R, C), generator=gen).float() / 8
+    score[1, ::3] = float("-inf")
+    score[2, ::2] = -0.0
+    score[2, 1::4] = 0.0
+    pool = G.alloc_pool(cfg, gpu_device)
+    pool["cand_score"].copy_(score)
+    pool["cand_tok"].copy_(torch.randint(0, 1000, (R, C), generator=gen).int())
+    pool["cand_parent"].fill_(-1)
+    pool["cand_depth"].fill_(1)
+    tree = G.gto_select_topg(cfg, pool, U.alloc_poisoned(G.alloc_tree, cfg, gpu_device))
+    torch.cuda.synchronize()
+    n = min(g, C)
+    for r in range(R):
+        want = sorted(range(C), key=lambda c: (-float(score[r, c]), c))[:n]
+        assert tree["sel_cand"][r, :n].tolist() == want
+        assert torch.equal(tree["sel_score"][r, :n].cpu(), score[r, want])
+        assert torch.equal(tree["sel_tok"][r, :n].cpu(), pool["cand_tok"][r].cpu()[want])
+    assert bool((tree["n_sel"] == n).all()) and bool((tree["sel_leaf"][:, :n] == 1).all())
