@@ -186,8 +186,8 @@ template <> struct LaneTop<uint16_t> {       // bf16: the group's number travels
     for (int i = 0; i < kTopGroups; ++i) k[i] = neg_inf();
   }
   __device__ __forceinline__ void add(float m, int group) {
-    // -inf would turn into a NaN: the lowest finite bf16 stands in for it
-    m = fmaxf(m, lowest());
+    // an infinity would turn into a NaN: the type's finite limits stand in for them
+    m = __builtin_amdgcn_fmed3f(m, lowest(), __uint_as_float(0x7f7f0000u));
     m = __uint_as_float(__float_as_uint(m) | (uint32_t)group);
 #pragma unroll
     for (int i = kTopGroups - 1; i > 0; --i) k[i] = __builtin_amdgcn_fmed3f(k[i - 1], k[i], m);

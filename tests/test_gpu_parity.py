@@ -569,3 +569,22 @@ def test_selection_with_ties(gpu_device, k, d, g, distinct):
         assert torch.equal(tree["sel_score"][r, :n].cpu(), score[r, want])
         assert torch.equal(tree["sel_tok"][r, :n].cpu(), pool["cand_tok"][r].cpu()[want])
     assert bool((tree["n_sel"] == n).all()) and bool((tree["sel_leaf"][:, :n] == 1).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_row_topk_with_infinite_logits(gpu_device, dtype):
+    """+inf is outside the contract for values, but it still ranks above everything finite."""
+    V, k = 9000, 10
+    x = torch.randn(V, generator=torch.Generator().manual_seed(5)).to(dtype)
+    x[[77, 8001]] = float("inf")
+    x[::7] = float("-inf")
+    x[77] = float("inf")
+    D = x.reshape(1, 1, 1, V).expand(1, 1, k, V).contiguous().to(gpu_device)
+    for waves in (1, 4):
+        cfg = G.make_config(R=1, d=1, k=k, g=4, V=V, dtype=dtype, waves_per_row=waves)
+        ds = G.gto_draft_row_stats(cfg, D, G.alloc_draft_stats(cfg, gpu_device))
+        ts = G.gto_target_row_stats(cfg, D, G.alloc_target_stats(cfg, gpu_device))
+        torch.cuda.synchronize()
+        xs = x.float()
+        assert ds["top_tok"][0, 0, 0].tolist() == sorted(range(V), key=lambda v: (-float(xs[v]), v))[:k]
+        assert int(ts["t_argmax"][0, 0, 0]) == 77
