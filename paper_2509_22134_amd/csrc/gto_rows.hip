@@ -8,8 +8,8 @@
 //                one fp32 gradient row  coef * (onehot - softmax).
 //
 // Both are HBM-bandwidth bound by design: per element they spend one conversion, one fused
-// multiply-add, one exp2 and one add; the top-k costs one max per element plus a rarely
-// taken insertion path.
+// multiply-add, one exp2 and one add; the top-k costs one max per element, a few operations per
+// group of them and a second read of the dozen groups that can hold it.
 #include <type_traits>
 
 #include "gto_device.h"
@@ -74,6 +74,16 @@ struct WaveAcc {
 // kDraftTopK: top-k collected at the end of the row (see LaneTop).  kDraftInsert: top-k kept in a sorted list while
 // streaming (large k, or a row with more groups than LaneTop can number).
 enum RowMode { kDraftTopK = 0, kTargetArgmax = 1, kLseOnly = 2, kDraftInsert = 3 };
+
+// The exponents are taken with the fp32 log2(e), which is 1.3e-8 of itself too small: what a lane summed, whose terms
+// lie near its maximum m, is that much times M - m too large against the row's maximum M, whose exponent the
+// log-sum-exp corrects exactly.  Rows of N(0, 4), V = 128 256: the log-probabilities are 5.8e-8 too low on average
+// without this, 2.3e-8 with it (26 112 rows of V = 32 000: 0.5 % slower; elsewhere the same).  (Lanes far below M, or
+// without any finite value, hold nothing that counts.)
+__device__ __forceinline__ double slope_fix(float m, float M) {
+  constexpr double kSlope = 1.0 - (double)kLog2e * 0.69314718055994530942;
+  return 1.0 + kSlope * (double)fmaxf(m - M, -256.f);
+}
 
 // Issues the LOADS 16-byte loads of one tile (lane l, load u: elements (u*64 + l)*EPV ...).
 template <typename T, int LOADS, bool GUARD>
@@ -355,8 +365,8 @@ __device__ __forceinline__ int first_of_max(const T *__restrict__ row, int V, fl
   return wave_min(id);
 }
 
-// What bounds it: memory, with the vector ALUs close behind (about 7.5 issue slots per logit, 4 of them the
-// quarter-rate exp2).  52 224 rows of V = 128 256 bf16 stream at 6.64 TB/s (target rows 6.86; a plain read reaches
+// What bounds it: memory, with the vector ALUs behind (6.7 issue slots per logit, 4 of them the quarter-rate exp2: 0.62
+// of their time).  52 224 rows of V = 128 256 bf16 stream at 6.57 to 6.68 TB/s (target rows 6.86; a plain read reaches
 // 7.0 to 7.1).  The next tile is requested before the current one is scanned, which matters where few waves
 // share a compute unit (196 rows of V = 151 936: 16.1 us without, 14.1 with).
 template <typename T, int WAVES, int LOADS, int MODE>
@@ -453,7 +463,7 @@ __global__ __launch_bounds__(WAVES *kWave) void k_row_stats(RowStatsArgs a) {
   }
 
   const float Mw = wave_max_dpp(acc.m);
-  const double Sw = wave_sum_dpp(acc.s);
+  const double Sw = wave_sum_dpp(acc.s * slope_fix(acc.m, Mw));
 
   __shared__ uint32_t sh_groups[WAVES * kTopGroups * kWave];
   __shared__ __align__(16) uint64_t sh_key[WAVES * kWave];      // each wave's sorted list
@@ -482,9 +492,10 @@ __global__ __launch_bounds__(WAVES *kWave) void k_row_stats(RowStatsArgs a) {
   if (WAVES > 1) {
     const bool on = lane < WAVES;
     const float wc = on ? sh_C[lane] : neg_inf();
-    M = wave_max_dpp(on ? sh_M[lane] : neg_inf());
+    const float wm = on ? sh_M[lane] : neg_inf();
+    M = wave_max_dpp(wm);
     C = wave_max_dpp(wc);
-    S = wave_sum_dpp(on ? scale_pow2(sh_S[lane], wc - C) : 0.0);
+    S = wave_sum_dpp(on ? scale_pow2(sh_S[lane], wc - C) * slope_fix(wm, M) : 0.0);
   }
   // log2-domain total is C + log2(S); the row maximum contributes exactly M*log2e of it.
   const double lse = (double)M + kLn2 * (((double)C - (double)M * (double)kLog2e) + log2(S));
