@@ -7,10 +7,10 @@
 // LDS or registers, global memory read in one or two rounds at the start and written once at the end.  Larger shapes
 // take the workgroup-per-root kernels.
 //
-// Ranking everywhere is on a packed 64-bit key (order-preserving bits of the fp32 score, then the
-// inverted index): keys are unique, so (score descending, index ascending) is realised exactly and
-// deterministically whether a rank is found by counting the keys that beat mine (expansion: k^2
-// keys per level) or by sorting (top-g: C keys).
+// Ranking everywhere is by the order-preserving bits of the fp32 score, then the inverted index, mostly packed into one
+// key: keys are unique, so (score descending, index ascending) is realised exactly and deterministically whether the
+// best are taken one after the other (expansion), a rank is found by counting the keys that beat mine (large k) or the
+// keys are sorted (top-g).
 #include <type_traits>
 
 #include "gto_device.h"
